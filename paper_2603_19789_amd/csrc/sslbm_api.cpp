@@ -496,8 +496,10 @@ sslbm_status bgk_run(sslbm_ctx *c, void *f, void *rhoD, void *f_scratch, void *r
     const hipStream_t s = (hipStream_t)hip_stream;
     const sslbm::GridDesc g = grid_of(c);
     void *fa = f, *da = rhoD, *fb = f_scratch, *db = rhoD_scratch;
-    for (long long n = 0; n < nsteps; ++n) {
-        st = hip_status(c, sslbm::launch_bgk_step(c->dtype, fa, da, fb, db, g, c->coef, s));
+    const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, sslbm::bgk_depth(c->dtype, g));
+    for (long long i = 0; i < plan.count; ++i) {
+        st = hip_status(c, sslbm::launch_bgk_pass(c->dtype, fa, da, fb, db, g, c->coef,
+                                                  plan.steps(i), s));
         if (st != SSLBM_OK)
             return st;
         void *t = fa;

@@ -82,6 +82,11 @@ hipError_t launch_bgk_init(int dtype, const void *rho, void *f, void *rhoD, cons
                            hipStream_t s);
 hipError_t launch_bgk_step(int dtype, const void *f_in, const void *rhoD_in, void *f_out,
                            void *rhoD_out, const GridDesc &g, const StepCoef &k, hipStream_t s);
+// Steps per pass bgk_run takes on this grid, and one pass of K steps.
+int bgk_depth(int dtype, const GridDesc &g);
+hipError_t launch_bgk_pass(int dtype, const void *f_in, const void *rhoD_in, void *f_out,
+                           void *rhoD_out, const GridDesc &g, const StepCoef &k, int K,
+                           hipStream_t s);
 hipError_t launch_bgk_density(int dtype, const void *f, const void *rhoD, void *rho,
                               const GridDesc &g, hipStream_t s);
 
