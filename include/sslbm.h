@@ -152,6 +152,10 @@ int sslbm_get_blocking(const sslbm_ctx *c);
  * wavefront (FP32 above 6 steps with two columns per lane; FP64 above 5 with
  * one, above 2 with two) returns SSLBM_E_UNSUPPORTED.
  * sslbm_get_launch reports the shape sslbm_run uses (automatic fields resolved).
+ * With every field automatic, sslbm_run takes grids of at most 1.4 million
+ * cells in FP32 (0.45 million in FP64) in passes of tiles held in registers
+ * instead, of up to 16 steps; the shape reported is then the one that passes
+ * of the march would have. sslbm_plan_run reports the passes either way.
  */
 typedef struct {
     int steps_per_pass;
@@ -167,8 +171,10 @@ sslbm_status sslbm_get_launch(const sslbm_ctx *c, sslbm_launch *shape);
  * NULL, receives it). Candidates: one and (for an even row length and
  * pair-aligned buffers) two columns per lane; every depth from 1 to the
  * register limit; rows_per_wave automatic (one round of resident
- * wavefronts) and 8, 16, 32, 64, 128 where at least twice the depth. Each
- * candidate runs one untimed and three timed passes rho -> scratch (device
+ * wavefronts) and 8, 16, 32, 64, 128 where at least twice the depth (on grids
+ * small enough for tiles also 1, 2 and 4, and the tiles themselves: if they are
+ * fastest, the context stays on automatic shapes and *best is the fastest march
+ * shape). Each candidate runs one untimed and three timed passes rho -> scratch (device
  * buffers of 5 * nx * ny elements, not overlapping): rho is only read,
  * scratch is overwritten. Timed with HIP events on hip_stream after
  * synchronizing it; the call returns when tuning is done. Useful where the
@@ -206,7 +212,8 @@ sslbm_status sslbm_run(sslbm_ctx *c, void *rho, void *scratch, long long nsteps,
 
 /*
  * How sslbm_run splits nsteps into passes with the context's current pass
- * shape: the fewest passes of at most steps_per_pass steps, one more if that
+ * shape: the fewest passes of at most steps_per_pass steps (of the depth chosen
+ * for nsteps where it takes tiles), one more if that
  * makes their count even and leaves every pass a step (the ping-pong then
  * ends in rho, with no copy), and the steps spread evenly over them: the
  * first passes take *longest steps, the rest *shortest (equal when the split
@@ -257,7 +264,7 @@ sslbm_status bgk_density(sslbm_ctx *c, const void *f, const void *rhoD, void *rh
  *       sslbm_step), work a device buffer of work_bytes >= the workspace
  *       size, caller-owned and clobbered. SSLBM_E_ARG for null pointers,
  *       negative nsteps, a short or misaligned buffer; SSLBM_E_ALIAS if rho
- *       and work overlap. Four launches per step, queued on hip_stream.
+ *       and work overlap. One launch per step, queued on hip_stream.
  */
 size_t sslbm_fd4_workspace_bytes(const sslbm_ctx *c);
 sslbm_status sslbm_fd4_run(sslbm_ctx *c, void *rho, void *work, size_t work_bytes, long long nsteps,

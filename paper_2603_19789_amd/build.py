@@ -20,7 +20,7 @@ ARCH = "gfx950"
 SOURCES = ["sslbm_api.cpp", "ensemble_api.cpp", "adjoint_api.cpp", "surrogate_api.cpp",
            "model_api.cpp", "sslbm_kernels.hip", "ensemble_kernels.hip", "adjoint_kernels.hip",
            "surrogate_kernels.hip", "model_kernels.hip", "bgk_kernels.hip",
-           "reduce_kernels.hip", "fd4_kernels.hip"]
+           "reduce_kernels.hip", "fd4_kernels.hip", "tile_kernels.hip"]
 
 # Sources compiled more than once, one object per set of definitions: the
 # generic-model kernels per arithmetic type and lattice (four objects that

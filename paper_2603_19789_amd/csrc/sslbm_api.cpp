@@ -48,10 +48,9 @@ sslbm_status hip_status(sslbm_ctx *c, hipError_t e) {
 int auto_depth(const sslbm_ctx *c) { return c->dtype == SSLBM_F32 ? 6 : 5; }
 int auto_cols(const sslbm_ctx *c) { return c->dtype == SSLBM_F32 ? 2 : 1; }
 
-// Rows per wavefront when the caller has not chosen: the shortest chunks for
-// which all wavefronts of the pass are resident at once (one round, no tail),
-// but at least 2K rows so the halo rows stay a minority. Without a device to
-// query, a fixed estimate of three resident wavefronts per SIMD is used.
+// Rows per wavefront for which all wavefronts of the pass are resident at once
+// (one round, no tail). Without a device to query, a fixed estimate of three
+// resident wavefronts per SIMD is used.
 long long round_rows(const sslbm_ctx *c, int K, int V) {
     const int w = sslbm::strip_width(K, V);
     const long long strips = (c->nx + w - 1) / w;
@@ -71,16 +70,40 @@ int auto_rows(const sslbm_ctx *c, int K, int V) {
     // FP32 4.44 -> 4.68 TB/s, FP64 4.54 -> 4.71 TB/s).
     if (K == 1 && h > 8)
         h = 8;
-    if (h < 2 * K)
-        h = 2 * K;
+    // Chunks shorter than 2K rows are mostly halo. A grid that cannot give
+    // every SIMD a wavefront of that height takes one wavefront per SIMD:
+    // its passes are bound by the length of one march (FP64 five steps, 256^2:
+    // 2 rows 1.57 us a step, 10 rows 2.8; 512^2: 6 rows 2.47, 3 rows 2.80).
+    if (h < 2 * K) {
+        const int w = sslbm::strip_width(K, V);
+        const long long strips = (c->nx + w - 1) / w;
+        const long long chunks = 4 * 256 / strips > 1 ? 4 * 256 / strips : 1;
+        const long long one = (c->ny + chunks - 1) / chunks;
+        if (h < one)
+            h = one;
+        if (h > 2 * K)
+            h = 2 * K;
+    }
     if (h > 65536)
         h = 65536;
     return (int)h;
 }
 
-// Pass shape actually used: requested fields, automatic ones filled in.
+bool automatic(const sslbm_launch &r) {
+    return r.steps_per_pass == 0 && r.rows_per_wave == 0 && r.cols_per_lane == 0;
+}
+
+// Tiles of a run of nsteps: none (rows = 0) where the caller has chosen a
+// march shape or the grid is too large for them.
+sslbm::TilePlan run_tiles(const sslbm_ctx *c, long long nsteps) {
+    if (!automatic(c->launch))
+        return sslbm::TilePlan();
+    return sslbm::tile_plan(c->dtype, &c->nx, &c->ny, 1, nsteps);
+}
+
+// March shape of a pass: requested fields, automatic ones filled in.
 sslbm_launch resolve(const sslbm_ctx *c) {
-    sslbm_launch r = c->launch;
+    sslbm_launch r = automatic(c->launch) ? c->tuned : c->launch;
     if (r.steps_per_pass == 0)
         r.steps_per_pass = auto_depth(c);
     if (r.cols_per_lane == 0) {
@@ -286,10 +309,12 @@ sslbm_status sslbm_set_launch(sslbm_ctx *c, const sslbm_launch *shape) {
     sslbm_ctx probe = *c;
     probe.partials = nullptr;
     probe.launch = r;
+    probe.tuned = sslbm_launch{};
     const sslbm_launch full = resolve(&probe);
     if (full.steps_per_pass > sslbm::march_max_depth(c->dtype, full.cols_per_lane))
         return SSLBM_E_UNSUPPORTED;
     c->launch = r;
+    c->tuned = sslbm_launch{};
     return SSLBM_OK;
 }
 
@@ -323,47 +348,66 @@ sslbm_status sslbm_tune(sslbm_ctx *c, const void *rho, void *scratch, void *hip_
     const uintptr_t pair = 2 * elem_size(c);
     const bool pairs_ok =
         c->nx % 2 == 0 && (uintptr_t)rho % pair == 0 && (uintptr_t)scratch % pair == 0;
-    const sslbm_launch saved = c->launch;
+    const sslbm_launch saved = c->launch, saved_tuned = c->tuned;
     sslbm_launch best_shape = resolve(c);
     double best_ns = 1e300;
+    // ns a step of `pass` (K steps, rho -> scratch): one untimed pass, then
+    // three timed ones
+    auto ns_per_step = [&](int K, auto pass) {
+        for (int rep = 0; rep < 4 && st == SSLBM_OK; ++rep) {
+            if (rep == 1)
+                st = hip_status(c, hipEventRecord(t0, s));
+            if (st == SSLBM_OK)
+                st = pass();
+        }
+        if (st == SSLBM_OK)
+            st = hip_status(c, hipEventRecord(t1, s));
+        if (st == SSLBM_OK)
+            st = hip_status(c, hipEventSynchronize(t1));
+        float ms = 0.f;
+        if (st == SSLBM_OK)
+            st = hip_status(c, hipEventElapsedTime(&ms, t0, t1));
+        return 1e6 * ms / (3.0 * K);
+    };
+    // Rows under twice the depth pay only on grids that leave SIMDs idle, the
+    // ones that the tiles are for; there the tiles are a candidate too.
+    const sslbm::TilePlan tiles = sslbm::tile_plan(c->dtype, &c->nx, &c->ny, 1, 1000);
     for (int V = 1; V <= (pairs_ok ? 2 : 1) && st == SSLBM_OK; ++V) {
         for (int K = 1; K <= sslbm::march_max_depth(c->dtype, V) && st == SSLBM_OK; ++K) {
-            const int cands[] = {0, 8, 16, 32, 64, 128};
+            const int cands[] = {0, 1, 2, 4, 8, 16, 32, 64, 128};
             for (int H : cands) {
-                if (H != 0 && H < 2 * K)
+                if (H != 0 && H < 2 * K && (H >= 8 || tiles.rows == 0))
                     continue;
                 c->launch = sslbm_launch{K, H, V};
-                // one untimed pass, then three timed ones, all rho -> scratch
-                for (int rep = 0; rep < 4 && st == SSLBM_OK; ++rep) {
-                    if (rep == 1)
-                        st = hip_status(c, hipEventRecord(t0, s));
-                    if (st == SSLBM_OK)
-                        st = sslbm::run_pass(c, rho, scratch, K, s);
-                }
-                if (st == SSLBM_OK)
-                    st = hip_status(c, hipEventRecord(t1, s));
-                if (st == SSLBM_OK)
-                    st = hip_status(c, hipEventSynchronize(t1));
-                float ms = 0.f;
-                if (st == SSLBM_OK)
-                    st = hip_status(c, hipEventElapsedTime(&ms, t0, t1));
+                const double ns =
+                    ns_per_step(K, [&] { return sslbm::run_pass(c, rho, scratch, K, s); });
                 if (st != SSLBM_OK)
                     break;
-                const double ns_per_step = 1e6 * ms / (3.0 * K);
-                if (ns_per_step < best_ns) {
-                    best_ns = ns_per_step;
+                if (ns < best_ns) {
+                    best_ns = ns;
                     best_shape = resolve(c);
                 }
             }
         }
     }
+    bool use_tiles = false;
+    if (st == SSLBM_OK && tiles.rows > 0) {
+        const sslbm::GridDesc g = grid_of(c);
+        const double ns = ns_per_step(tiles.depth, [&] {
+            return hip_status(c, sslbm::launch_tile(c->dtype, rho, scratch, g, c->coef,
+                                                    tiles.depth, tiles.rows, s));
+        });
+        use_tiles = st == SSLBM_OK && ns < best_ns;
+    }
     (void)hipEventDestroy(t0);
     (void)hipEventDestroy(t1);
     if (st != SSLBM_OK) {
         c->launch = saved;
+        c->tuned = saved_tuned;
         return st;
     }
-    c->launch = best_shape;
+    c->launch = use_tiles ? sslbm_launch{} : best_shape;
+    c->tuned = best_shape;
     if (best)
         *best = best_shape;
     return SSLBM_OK;
@@ -373,7 +417,9 @@ sslbm_status sslbm_plan_run(const sslbm_ctx *c, long long nsteps, long long *pas
                             int *shortest) {
     if (!c || nsteps < 0 || !passes)
         return SSLBM_E_ARG;
-    const sslbm::PassPlan p = sslbm::plan_passes(nsteps, resolve(c).steps_per_pass);
+    const sslbm::TilePlan tiles = run_tiles(c, nsteps);
+    const sslbm::PassPlan p =
+        sslbm::plan_passes(nsteps, tiles.rows ? tiles.depth : resolve(c).steps_per_pass);
     *passes = p.count;
     if (longest)
         *longest = p.count == 0 ? 0 : p.steps(0);
@@ -415,16 +461,18 @@ sslbm_status sslbm_run(sslbm_ctx *c, void *rho, void *scratch, long long nsteps,
         return SSLBM_E_ALIAS;
     if (nsteps == 0)
         return SSLBM_OK;
-    const int K = resolve(c).steps_per_pass;
+    const sslbm::TilePlan tiles = run_tiles(c, nsteps);
+    const int K = tiles.rows ? tiles.depth : resolve(c).steps_per_pass;
     const hipStream_t s = (hipStream_t)hip_stream;
     const sslbm::GridDesc g = grid_of(c);
     void *src = rho, *dst = scratch;
     const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, K);
     for (long long i = 0; i < plan.count; ++i) {
         const int k = plan.steps(i);
-        const sslbm_status st =
-            hip_status(c, sslbm::launch_march(c->dtype, src, dst, g, c->coef, k,
-                                              shape_for(c, k, src, dst), s));
+        const sslbm_status st = hip_status(
+            c, tiles.rows ? sslbm::launch_tile(c->dtype, src, dst, g, c->coef, k, tiles.rows, s)
+                          : sslbm::launch_march(c->dtype, src, dst, g, c->coef, k,
+                                                shape_for(c, k, src, dst), s));
         if (st != SSLBM_OK)
             return st;
         void *t = src;

@@ -77,6 +77,21 @@ int strip_width(int K, int cols_per_lane);
 // once (occupancy x CUs), 0 when no device can be queried.
 int march_resident_waves(int dtype, int K, int cols_per_lane, bool diffuse_d);
 
+// ---- register tiles (tile_kernels.hip) -----------------------------------
+// Most steps a tile takes in one pass (its halo leaves 32 of 64 columns).
+constexpr int TILE_MAX_DEPTH = 16;
+// Tile height (rows a lane) and steps per pass for a run of nsteps on `count`
+// grids that advance together; rows = 0: the grids are too large, march.
+struct TilePlan {
+    int rows = 0;
+    int depth = 0;
+};
+TilePlan tile_plan(int dtype, const int *nx, const int *ny, int count, long long nsteps);
+long long tile_count(int nx, int ny, int R, int K);
+// K steps in -> out (no overlap) with R rows a lane.
+hipError_t launch_tile(int dtype, const void *in, void *out, const GridDesc &g, const StepCoef &k,
+                       int K, int R, hipStream_t s);
+
 // ---- launchers (bgk_kernels.hip) ----------------------------------------
 hipError_t launch_bgk_init(int dtype, const void *rho, void *f, void *rhoD, const GridDesc &g,
                            hipStream_t s);
@@ -104,6 +119,7 @@ struct sslbm_ctx {
     sslbm_params p{};
     sslbm::StepCoef coef{};
     sslbm_launch launch{};  // requested pass shape; zero fields = automatic
+    sslbm_launch tuned{};   // march shape the tuner found, reported while launch is all automatic
     int last_hip = 0;
     double *partials = nullptr;  // device buffer of sslbm_total
     int partial_blocks = 0;
