@@ -11,10 +11,19 @@
 //    2, 4, ..., 512, 1024, ...): passes of the tile-table kernel with a pass
 //    shape (steps per pass, rows per wavefront, columns per lane) of their
 //    own, automatic or tuned per class.
-// A run gives every class its own chain of launches on its own stream,
-// forked from and joined back to the caller's stream (or captured as
-// parallel branches of one HIP graph): classes never wait for each other,
-// only for their own previous pass.
+// A run is one or more chains of launches, side by side on streams of their
+// own, forked from and joined back to the caller's stream (or parallel
+// branches of one HIP graph); chains never wait for each other. The on-chip
+// class is a chain. The march classes are
+//  * one chain of register-tile passes over all of them, where their shapes
+//    are automatic and they hold too few cells for marches;
+//  * one chain of passes over all of them, where they have the same steps per
+//    pass and columns per lane (the automatic shapes do, as a rule): one
+//    launch per pass fills the GPU by itself, while a stream per class shares
+//    hardware queues with the others, so that classes wait for each other
+//    (96 grids of 64^2 to 512^2, FP32: 4.9 ms for 200 steps with three march
+//    chains, 3.0 ms with one);
+//  * else a chain per class.
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
@@ -39,6 +48,7 @@ constexpr long long ALIGN_ELEMS = 4;
 struct TileTable {
     sslbm::EnsTile *dev = nullptr;
     int count = 0;
+    int V = 0;  // columns per lane of a march table
 };
 
 struct GraphKey {
@@ -56,6 +66,7 @@ struct EnsClass {
     long long cells = 0;
     int max_side = 0;
     bool even_rows = true;  // every row length even (two columns per lane possible)
+    std::vector<sslbm::GridSize> sizes;  // distinct sizes of the instances
     sslbm_launch launch{};  // requested pass shape, zero fields automatic
     hipStream_t stream = nullptr;
     hipEvent_t done = nullptr;
@@ -72,13 +83,16 @@ struct sslbm_ensemble {
     bool diffuse_d = false;
     std::vector<EnsClass> classes;  // march classes by bucket, then the on-chip class
     std::vector<int> class_of;      // class of every instance
-    long long march_cells = 0;
+    int march_max_side = 0;
     size_t lds_bytes = 0;  // the largest on-chip instance
     int last_hip = 0;
     int device = -1;
     void *insts = nullptr;    // device instance table
     int *lds_list = nullptr;  // device list of the on-chip instances
-    std::map<std::tuple<int, int, int, int>, TileTable> tiles;  // (class, k, H, V) -> table
+    std::vector<sslbm::GridSize> march_sizes;  // distinct sizes of the march classes' grids
+    // tables of a chain's passes: {steps, columns per lane, then class and rows
+    // per wavefront of each march class}, or {steps, 0, rows a lane, classes}
+    std::map<std::vector<int>, TileTable> tiles;
     hipStream_t stream = nullptr;  // graph and tuning stream
     hipEvent_t ev_in = nullptr, ev_out = nullptr, ev_fork = nullptr;
     std::map<GraphKey, hipGraphExec_t> graphs;
@@ -101,22 +115,23 @@ bool valid_class(const sslbm_ensemble *e, int c) {
 
 // Tiles of one pass of k steps of class c: every instance of the class cut
 // into strips of strip_width(k, V) output columns and chunks of H output rows.
-std::vector<sslbm::EnsTile> make_tiles(const sslbm_ensemble *e, int c, int k, int H, int V) {
-    std::vector<sslbm::EnsTile> t;
+void march_tiles(const sslbm_ensemble *e, int c, int k, int H, int V,
+                 std::vector<sslbm::EnsTile> *t) {
     const int w = sslbm::strip_width(k, V);
     for (int i : e->classes[c].insts)
         for (int y0 = 0; y0 < e->ny[i]; y0 += H)
             for (int x0 = 0; x0 < e->nx[i]; x0 += w)
-                t.push_back({i, x0, y0, std::min(y0 + H, e->ny[i]), (y0 / H) & 1});
-    return t;
+                t->push_back({i, x0, y0, std::min(y0 + H, e->ny[i]), (y0 / H) & 1});
 }
 
-long long count_tiles(const sslbm_ensemble *e, int c, int k, int H, int V) {
-    const int w = sslbm::strip_width(k, V);
-    long long n = 0;
+// Register tiles of one pass of k steps of class c, R rows a lane.
+void register_tiles(const sslbm_ensemble *e, int c, int k, int R,
+                    std::vector<sslbm::EnsTile> *t) {
+    const int w = 64 - 2 * k, h = sslbm::TILE_WAVES * R - 2 * k;
     for (int i : e->classes[c].insts)
-        n += (long long)((e->nx[i] + w - 1) / w) * ((e->ny[i] + H - 1) / H);
-    return n;
+        for (int y0 = 0; y0 < e->ny[i]; y0 += h)
+            for (int x0 = 0; x0 < e->nx[i]; x0 += w)
+                t->push_back({i, x0, y0, 0, 0});
 }
 
 // Columns per lane actually usable: two need every row length of the class
@@ -128,33 +143,62 @@ int usable_cols(const sslbm_ensemble *e, int c, int V, int k, bool pairs_ok) {
     return V;
 }
 
+// Strips of w output columns and chunks of H output rows of grids of some sizes.
+long long count_tiles(const std::vector<sslbm::GridSize> &sizes, int w, int H) {
+    long long n = 0;
+    for (const sslbm::GridSize &z : sizes)
+        n += (long long)((z.nx + w - 1) / w) * ((z.ny + H - 1) / H) * z.count;
+    return n;
+}
+
+// Automatic columns per lane of the march classes, one number for all of them
+// (so that they can share a launch): two halve the shifts per cell (about 7%:
+// 40 grids of 512^2 556 against 519 GLUPS), unless their strips, twice as
+// wide, cover more columns past the edges than that (256^2: 293 against 352;
+// 128^2 to 512^2 mixed: 443 against 474).
+int auto_cols(const sslbm_ensemble *e, int K) {
+    if (e->dtype != SSLBM_F32 || K > sslbm::march_max_depth(e->dtype, 2))
+        return 1;
+    long long covered[2] = {0, 0};
+    for (int V = 1; V <= 2; ++V) {
+        const int w = sslbm::strip_width(K, V);
+        for (const sslbm::GridSize &z : e->march_sizes)
+            covered[V - 1] += (long long)((z.nx + w - 1) / w) * 64 * V * z.ny * z.count;
+    }
+    return covered[1] <= covered[0] + covered[0] / 32 ? 2 : 1;
+}
+
 // Pass shape of march class c: requested fields, automatic ones filled in.
-// Automatic: the single-grid depth; two columns per lane where the longest
-// side exceeds one two-column strip (narrower grids waste most of it); rows
-// per wavefront the fewest for which the class's tiles fit its share of the
-// resident wavefronts (its share of the march cells, since the classes run
-// side by side).
-sslbm_launch resolve(const sslbm_ensemble *e, int c, bool pairs_ok = true) {
+// Automatic: the single-grid depth; columns as above; rows per wavefront the
+// fewest, at least 16, for which the tiles of every march class (of class c
+// alone where it runs alone) are resident at once. The same rows for all
+// classes: a pass lasts as long as its longest march, and with rows by each
+// class's share of the GPU the smallest class had the tallest ones (96 grids
+// of 64^2 to 512^2: 390 GLUPS against 474).
+sslbm_launch resolve(const sslbm_ensemble *e, int c, bool pairs_ok = true, bool alone = false) {
     const EnsClass &cl = e->classes[c];
     sslbm_launch r = cl.launch;
     if (r.steps_per_pass == 0)
         r.steps_per_pass = e->dtype == SSLBM_F32 ? 6 : 5;
-    if (r.cols_per_lane == 0)
-        r.cols_per_lane =
-            e->dtype == SSLBM_F32 && cl.max_side > sslbm::strip_width(r.steps_per_pass, 2) ? 2
-                                                                                           : 1;
+    if (r.cols_per_lane == 0) {
+        r.cols_per_lane = auto_cols(e, r.steps_per_pass);
+        for (int i = 0; i < (int)e->classes.size(); ++i)
+            if (!e->classes[i].on_chip)
+                r.cols_per_lane = std::min(
+                    r.cols_per_lane, usable_cols(e, i, r.cols_per_lane, r.steps_per_pass, pairs_ok));
+    }
     r.cols_per_lane = usable_cols(e, c, r.cols_per_lane, r.steps_per_pass, pairs_ok);
     if (r.rows_per_wave == 0) {
         long long resident =
             sslbm::march_resident_waves(e->dtype, r.steps_per_pass, r.cols_per_lane, e->diffuse_d);
         if (resident <= 0)
             resident = 2 * 4 * 256;
-        const double share = e->march_cells > 0 ? (double)cl.cells / (double)e->march_cells : 1.0;
-        const long long target = std::max(64ll, (long long)(share * (double)resident));
-        int lo = 2 * r.steps_per_pass, hi = std::max(lo, cl.max_side);
-        while (lo < hi) {  // smallest H with count_tiles(H) <= target
+        const std::vector<sslbm::GridSize> &sizes = alone ? cl.sizes : e->march_sizes;
+        const int w = sslbm::strip_width(r.steps_per_pass, r.cols_per_lane);
+        int lo = std::max(16, 2 * r.steps_per_pass), hi = std::max(lo, e->march_max_side);
+        while (lo < hi) {  // smallest H with count_tiles(H) <= resident
             const int mid = lo + (hi - lo) / 2;
-            if (count_tiles(e, c, r.steps_per_pass, mid, r.cols_per_lane) <= target)
+            if (count_tiles(sizes, w, mid) <= resident)
                 hi = mid;
             else
                 lo = mid + 1;
@@ -171,6 +215,16 @@ int main_class(const sslbm_ensemble *e) {
         if (!e->classes[c].on_chip && (best < 0 || e->classes[c].cells > e->classes[best].cells))
             best = c;
     return best;
+}
+
+// One more grid of nx x ny in a list of distinct sizes; `at` finds a size's
+// entry in the list of owner `id`.
+void count_size(std::vector<sslbm::GridSize> *sizes,
+                std::map<std::tuple<int, int, int>, size_t> *at, int id, int nx, int ny) {
+    const auto it = at->emplace(std::make_tuple(id, nx, ny), sizes->size());
+    if (it.second)
+        sizes->push_back(sslbm::GridSize{nx, ny, 0});
+    ++(*sizes)[it.first->second].count;
 }
 
 void drop_graphs(sslbm_ensemble *e) {
@@ -229,13 +283,96 @@ sslbm_status ensure_device_tables(sslbm_ensemble *e) {
     return SSLBM_OK;
 }
 
-sslbm_status tile_table(sslbm_ensemble *e, int c, int k, int H, int V, TileTable **out) {
-    auto key = std::make_tuple(c, k, H, V);
+// One chain of passes over some march classes: register tiles (tiles.rows > 0),
+// or marches of K steps with V columns per lane and H rows of each class.
+struct Chain {
+    std::vector<int> classes;
+    sslbm::TilePlan tiles;
+    int K = 0, V = 0;
+    std::vector<int> H;
+    int depth() const { return tiles.rows ? tiles.depth : K; }
+};
+
+// The march chains of a run of nsteps.
+std::vector<Chain> march_chains(const sslbm_ensemble *e, long long nsteps, bool pairs_ok) {
+    std::vector<Chain> out;
+    bool automatic = true, alike = true;
+    for (int c = 0; c < (int)e->classes.size(); ++c) {
+        const EnsClass &cl = e->classes[c];
+        if (cl.on_chip)
+            continue;
+        automatic = automatic && cl.launch.steps_per_pass == 0 && cl.launch.rows_per_wave == 0 &&
+                    cl.launch.cols_per_lane == 0;
+        const sslbm_launch r = resolve(e, c, pairs_ok);
+        Chain ch;
+        ch.classes = {c};
+        ch.K = r.steps_per_pass;
+        ch.V = r.cols_per_lane;
+        ch.H = {r.rows_per_wave};
+        alike = alike && (out.empty() || (out[0].K == ch.K && out[0].V == ch.V));
+        out.push_back(ch);
+    }
+    if (out.empty())
+        return out;
+    sslbm::TilePlan tiles;
+    if (automatic)
+        tiles = sslbm::tile_plan(e->dtype, e->march_sizes.data(), (int)e->march_sizes.size(),
+                                 nsteps);
+    if (tiles.rows || alike) {
+        for (size_t i = 1; i < out.size(); ++i) {
+            out[0].classes.push_back(out[i].classes[0]);
+            out[0].H.push_back(out[i].H[0]);
+        }
+        out.resize(1);
+        out[0].tiles = tiles;
+    }
+    return out;
+}
+
+// The chain of one march class run on its own.
+Chain class_chain(const sslbm_ensemble *e, int c, long long nsteps, bool pairs_ok) {
+    const EnsClass &cl = e->classes[c];
+    const sslbm_launch r = resolve(e, c, pairs_ok, true);
+    Chain ch;
+    ch.classes = {c};
+    ch.K = r.steps_per_pass;
+    ch.V = r.cols_per_lane;
+    ch.H = {r.rows_per_wave};
+    if (cl.launch.steps_per_pass == 0 && cl.launch.rows_per_wave == 0 &&
+        cl.launch.cols_per_lane == 0)
+        ch.tiles = sslbm::tile_plan(e->dtype, cl.sizes.data(), (int)cl.sizes.size(), nsteps);
+    return ch;
+}
+
+// The table of a pass of k steps of a chain, built on first use.
+sslbm_status chain_table(sslbm_ensemble *e, const Chain &ch, int k, bool pairs_ok,
+                         TileTable **out) {
+    int V = ch.V;
+    for (int c : ch.classes)
+        V = std::min(V, usable_cols(e, c, ch.V, k, pairs_ok));
+    std::vector<int> key;
+    if (ch.tiles.rows) {
+        key = {k, 0, ch.tiles.rows};
+        key.insert(key.end(), ch.classes.begin(), ch.classes.end());
+    } else {
+        key = {k, V};
+        for (size_t i = 0; i < ch.classes.size(); ++i) {
+            key.push_back(ch.classes[i]);
+            key.push_back(ch.H[i]);
+        }
+    }
     auto it = e->tiles.find(key);
     if (it == e->tiles.end()) {
-        const std::vector<sslbm::EnsTile> t = make_tiles(e, c, k, H, V);
+        std::vector<sslbm::EnsTile> t;
+        for (size_t i = 0; i < ch.classes.size(); ++i) {
+            if (ch.tiles.rows)
+                register_tiles(e, ch.classes[i], k, ch.tiles.rows, &t);
+            else
+                march_tiles(e, ch.classes[i], k, ch.H[i], V, &t);
+        }
         TileTable tab;
         tab.count = (int)t.size();
+        tab.V = V;
         sslbm_status st =
             hip_status(e, hipMalloc((void **)&tab.dev, sizeof(sslbm::EnsTile) * t.size()));
         if (st != SSLBM_OK)
@@ -252,79 +389,103 @@ sslbm_status tile_table(sslbm_ensemble *e, int c, int k, int H, int V, TileTable
     return SSLBM_OK;
 }
 
-// Enqueue nsteps steps of class c on stream s (tables must exist).
-sslbm_status enqueue_class(sslbm_ensemble *e, int c, void *rho, void *scratch, long long nsteps,
-                           bool pairs_ok, hipStream_t s) {
-    const EnsClass &cl = e->classes[c];
-    if (cl.on_chip)
-        return hip_status(e, sslbm::launch_ensemble_lds(
-                                 e->dtype, rho, e->lds_list, (int)cl.insts.size(), e->insts,
-                                 e->bc, nsteps, e->diffuse_d, e->lds_bytes, s));
-    const sslbm_launch r = resolve(e, c, pairs_ok);
+// One pass of k steps of a chain, src -> dst.
+sslbm_status enqueue_pass(sslbm_ensemble *e, const Chain &ch, const void *src, void *dst, int k,
+                          bool pairs_ok, hipStream_t s) {
+    TileTable *tab = nullptr;
+    const sslbm_status st = chain_table(e, ch, k, pairs_ok, &tab);
+    if (st != SSLBM_OK)
+        return st;
+    if (ch.tiles.rows)
+        return hip_status(e, sslbm::launch_ensemble_tiles(e->dtype, src, dst, tab->dev, tab->count,
+                                                          e->insts, e->bc, k, ch.tiles.rows,
+                                                          e->diffuse_d, s));
+    return hip_status(e, sslbm::launch_ensemble(e->dtype, src, dst, tab->dev, tab->count, e->insts,
+                                                e->bc, k, tab->V, e->diffuse_d, s));
+}
+
+// Enqueue nsteps steps of a chain on stream s (tables must exist).
+sslbm_status enqueue_chain(sslbm_ensemble *e, const Chain &ch, void *rho, void *scratch,
+                           long long nsteps, bool pairs_ok, hipStream_t s) {
     void *src = rho, *dst = scratch;
-    const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, r.steps_per_pass);
+    const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, ch.depth());
     for (long long i = 0; i < plan.count; ++i) {
-        const int k = plan.steps(i);
-        const int V = usable_cols(e, c, r.cols_per_lane, k, pairs_ok);
-        TileTable *tab = nullptr;
-        sslbm_status st = tile_table(e, c, k, r.rows_per_wave, V, &tab);
-        if (st != SSLBM_OK)
-            return st;
-        st = hip_status(e, sslbm::launch_ensemble(e->dtype, src, dst, tab->dev, tab->count,
-                                                  e->insts, e->bc, k, V, e->diffuse_d, s));
+        const sslbm_status st = enqueue_pass(e, ch, src, dst, plan.steps(i), pairs_ok, s);
         if (st != SSLBM_OK)
             return st;
         std::swap(src, dst);
     }
-    if (src != rho) {  // an odd number of passes: copy the class's instances back
+    if (src != rho) {  // an odd number of passes: copy the chain's instances back
         const size_t eb = elem_bytes(e);
-        for (int i : cl.insts) {
-            const size_t off = (size_t)e->offset[i] * eb;
-            const sslbm_status st = hip_status(
-                e, hipMemcpyAsync(static_cast<char *>(rho) + off, static_cast<char *>(src) + off,
-                                  5 * (size_t)e->nx[i] * e->ny[i] * eb, hipMemcpyDeviceToDevice,
-                                  s));
-            if (st != SSLBM_OK)
-                return st;
-        }
+        for (int c : ch.classes)
+            for (int i : e->classes[c].insts) {
+                const size_t off = (size_t)e->offset[i] * eb;
+                const sslbm_status st = hip_status(
+                    e, hipMemcpyAsync(static_cast<char *>(rho) + off,
+                                      static_cast<char *>(src) + off,
+                                      5 * (size_t)e->nx[i] * e->ny[i] * eb,
+                                      hipMemcpyDeviceToDevice, s));
+                if (st != SSLBM_OK)
+                    return st;
+            }
     }
     return SSLBM_OK;
 }
 
-// Every class on its own stream, forked from and joined back to s.
-sslbm_status enqueue_run(sslbm_ensemble *e, void *rho, void *scratch, long long nsteps,
-                         bool pairs_ok, hipStream_t s) {
-    if (e->classes.size() == 1)
-        return enqueue_class(e, 0, rho, scratch, nsteps, pairs_ok, s);
-    sslbm_status st = hip_status(e, hipEventRecord(e->ev_fork, s));
-    for (size_t c = 0; c < e->classes.size() && st == SSLBM_OK; ++c) {
-        EnsClass &cl = e->classes[c];
+sslbm_status enqueue_on_chip(sslbm_ensemble *e, const EnsClass &cl, void *rho, long long nsteps,
+                             hipStream_t s) {
+    return hip_status(e, sslbm::launch_ensemble_lds(e->dtype, rho, e->lds_list,
+                                                    (int)cl.insts.size(), e->insts, e->bc, nsteps,
+                                                    e->diffuse_d, e->lds_bytes, s));
+}
+
+// Every chain of a run: the first march chain on s itself, every other chain
+// on the stream of its (first) class, forked from and joined back to s.
+sslbm_status enqueue_run(sslbm_ensemble *e, const std::vector<Chain> &chains, void *rho,
+                         void *scratch, long long nsteps, bool pairs_ok, hipStream_t s) {
+    const EnsClass *on_chip = nullptr;
+    for (const EnsClass &cl : e->classes)
+        if (cl.on_chip)
+            on_chip = &cl;
+    if (chains.empty())
+        return on_chip ? enqueue_on_chip(e, *on_chip, rho, nsteps, s) : SSLBM_OK;
+    sslbm_status st = SSLBM_OK;
+    const bool forks = on_chip || chains.size() > 1;
+    if (forks)
+        st = hip_status(e, hipEventRecord(e->ev_fork, s));
+    std::vector<const EnsClass *> side;
+    if (on_chip)
+        side.push_back(on_chip);
+    for (size_t i = 1; i < chains.size(); ++i)
+        side.push_back(&e->classes[chains[i].classes[0]]);
+    for (size_t i = 0; i < side.size() && st == SSLBM_OK; ++i) {
+        const EnsClass &cl = *side[i];
         st = hip_status(e, hipStreamWaitEvent(cl.stream, e->ev_fork, 0));
         if (st == SSLBM_OK)
-            st = enqueue_class(e, (int)c, rho, scratch, nsteps, pairs_ok, cl.stream);
+            st = cl.on_chip ? enqueue_on_chip(e, cl, rho, nsteps, cl.stream)
+                            : enqueue_chain(e, chains[i + 1 - (on_chip ? 1 : 0)], rho, scratch,
+                                            nsteps, pairs_ok, cl.stream);
         if (st == SSLBM_OK)
             st = hip_status(e, hipEventRecord(cl.done, cl.stream));
-        if (st == SSLBM_OK)
-            st = hip_status(e, hipStreamWaitEvent(s, cl.done, 0));
     }
+    if (st == SSLBM_OK)
+        st = enqueue_chain(e, chains[0], rho, scratch, nsteps, pairs_ok, s);
+    for (size_t i = 0; i < side.size() && st == SSLBM_OK; ++i)
+        st = hip_status(e, hipStreamWaitEvent(s, side[i]->done, 0));
     return st;
 }
 
-// Build every tile table a run of nsteps will use (before any capture): a
-// class's run uses at most two depths, the longer and the shorter passes.
-sslbm_status prepare_run(sslbm_ensemble *e, long long nsteps, bool pairs_ok) {
-    for (int c = 0; c < (int)e->classes.size(); ++c) {
-        if (e->classes[c].on_chip)
-            continue;
-        const sslbm_launch r = resolve(e, c, pairs_ok);
-        const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, r.steps_per_pass);
+// Build every table a run of nsteps will use (before any capture): a chain's
+// run uses at most two depths, the longer and the shorter passes.
+sslbm_status prepare_chains(sslbm_ensemble *e, const std::vector<Chain> &chains, long long nsteps,
+                            bool pairs_ok) {
+    for (const Chain &ch : chains) {
+        const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, ch.depth());
         for (long long i : {0ll, plan.count - 1}) {
             if (i < 0)
                 continue;
-            const int k = plan.steps(i);
             TileTable *tab = nullptr;
-            const sslbm_status st = tile_table(e, c, k, r.rows_per_wave,
-                                      usable_cols(e, c, r.cols_per_lane, k, pairs_ok), &tab);
+            const sslbm_status st = chain_table(e, ch, plan.steps(i), pairs_ok, &tab);
             if (st != SSLBM_OK)
                 return st;
         }
@@ -353,40 +514,39 @@ sslbm_status check_shape(const sslbm_ensemble *e, const sslbm_launch &r) {
     return SSLBM_OK;
 }
 
-// One pass of every march class side by side (each on its own stream,
-// forked from and joined back to the ensemble's stream), rho -> scratch, with
-// the classes' current shapes: one untimed round, then three timed ones.
+// One pass of every march chain side by side (each on its own stream, forked
+// from and joined back to the ensemble's stream), rho -> scratch, with the
+// classes' current shapes: one untimed round, then three timed ones.
 // Returns the joint rate in cell-updates per nanosecond (0 on error).
 double joint_rate(sslbm_ensemble *e, const void *rho, void *scratch, bool pairs_ok,
                   hipEvent_t t0, hipEvent_t t1, sslbm_status *status) {
     sslbm_status st = SSLBM_OK;
+    const std::vector<Chain> chains = march_chains(e, 1000, pairs_ok);
     double work = 0.0;  // cell-updates of one round
+    for (const Chain &ch : chains)
+        for (int c : ch.classes)
+            work += (double)e->classes[c].cells * ch.depth();
     for (int rep = 0; rep < 4 && st == SSLBM_OK; ++rep) {
         if (rep == 1)
             st = hip_status(e, hipEventRecord(t0, e->stream));
-        if (st == SSLBM_OK)
+        if (st == SSLBM_OK && chains.size() > 1)
             st = hip_status(e, hipEventRecord(e->ev_fork, e->stream));
-        for (int c = 0; c < (int)e->classes.size() && st == SSLBM_OK; ++c) {
-            EnsClass &cl = e->classes[c];
-            if (cl.on_chip)
+        for (size_t i = 0; i < chains.size() && st == SSLBM_OK; ++i) {
+            const Chain &ch = chains[i];
+            EnsClass &cl = e->classes[ch.classes[0]];
+            if (i == 0) {
+                st = enqueue_pass(e, ch, rho, scratch, ch.depth(), pairs_ok, e->stream);
                 continue;
-            const sslbm_launch r = resolve(e, c, pairs_ok);
-            TileTable *tab = nullptr;
-            st = tile_table(e, c, r.steps_per_pass, r.rows_per_wave, r.cols_per_lane, &tab);
+            }
+            st = hip_status(e, hipStreamWaitEvent(cl.stream, e->ev_fork, 0));
             if (st == SSLBM_OK)
-                st = hip_status(e, hipStreamWaitEvent(cl.stream, e->ev_fork, 0));
-            if (st == SSLBM_OK)
-                st = hip_status(e, sslbm::launch_ensemble(e->dtype, rho, scratch, tab->dev,
-                                                          tab->count, e->insts, e->bc,
-                                                          r.steps_per_pass, r.cols_per_lane,
-                                                          e->diffuse_d, cl.stream));
+                st = enqueue_pass(e, ch, rho, scratch, ch.depth(), pairs_ok, cl.stream);
             if (st == SSLBM_OK)
                 st = hip_status(e, hipEventRecord(cl.done, cl.stream));
-            if (st == SSLBM_OK)
-                st = hip_status(e, hipStreamWaitEvent(e->stream, cl.done, 0));
-            if (rep == 0)
-                work += (double)cl.cells * r.steps_per_pass;
         }
+        for (size_t i = 1; i < chains.size() && st == SSLBM_OK; ++i)
+            st = hip_status(
+                e, hipStreamWaitEvent(e->stream, e->classes[chains[i].classes[0]].done, 0));
     }
     if (st == SSLBM_OK)
         st = hip_status(e, hipEventRecord(t1, e->stream));
@@ -414,7 +574,8 @@ std::vector<sslbm_launch> candidates(const sslbm_ensemble *e, int c, bool pairs_
 
 // The tuner: first one shape for every march class (the best joint rate),
 // then each class in turn, largest first, tries its candidates while the
-// others keep theirs, and keeps whichever raises the joint rate.
+// others keep theirs, and keeps whichever raises the joint rate. Where
+// automatic shapes mean register tiles, these are tried too, last.
 sslbm_status tune_classes(sslbm_ensemble *e, const void *rho, void *scratch, bool pairs_ok,
                           hipEvent_t t0, hipEvent_t t1) {
     std::vector<int> march;
@@ -442,7 +603,7 @@ sslbm_status tune_classes(sslbm_ensemble *e, const void *rho, void *scratch, boo
     for (int c : march)
         e->classes[c].launch = common;
     if (march.size() == 1)
-        return SSLBM_OK;
+        march.clear();
     for (int c : march) {
         sslbm_launch keep = e->classes[c].launch;
         for (const sslbm_launch &cand : candidates(e, c, pairs_ok)) {
@@ -456,6 +617,19 @@ sslbm_status tune_classes(sslbm_ensemble *e, const void *rho, void *scratch, boo
             }
         }
         e->classes[c].launch = keep;
+    }
+    if (sslbm::tile_plan(e->dtype, e->march_sizes.data(), (int)e->march_sizes.size(), 1000).rows) {
+        std::vector<sslbm_launch> keep;
+        for (EnsClass &cl : e->classes) {
+            keep.push_back(cl.launch);
+            cl.launch = sslbm_launch{};
+        }
+        const double rate = joint_rate(e, rho, scratch, pairs_ok, t0, t1, &st);
+        if (st != SSLBM_OK)
+            return st;
+        if (rate <= best)
+            for (size_t c = 0; c < e->classes.size(); ++c)
+                e->classes[c].launch = keep[c];
     }
     return SSLBM_OK;
 }
@@ -534,6 +708,7 @@ sslbm_status sslbm_ensemble_create(sslbm_ensemble **out, int count, const int *n
         e->classes.push_back(cl);
     }
     e->class_of.assign(count, -1);
+    std::map<std::tuple<int, int, int>, size_t> at_class, at_all;
     for (int i = 0; i < count; ++i) {
         int c;
         if (5 * (size_t)nx[i] * ny[i] * eb <= (size_t)sslbm::ENS_LDS_BYTES) {
@@ -551,8 +726,11 @@ sslbm_status sslbm_ensemble_create(sslbm_ensemble **out, int count, const int *n
         cl.cells += (long long)nx[i] * ny[i];
         cl.max_side = std::max(cl.max_side, std::max(nx[i], ny[i]));
         cl.even_rows = cl.even_rows && nx[i] % 2 == 0;
-        if (!cl.on_chip)
-            e->march_cells += (long long)nx[i] * ny[i];
+        if (!cl.on_chip) {
+            e->march_max_side = std::max(e->march_max_side, std::max(nx[i], ny[i]));
+            count_size(&cl.sizes, &at_class, c, nx[i], ny[i]);
+            count_size(&e->march_sizes, &at_all, 0, nx[i], ny[i]);
+        }
     }
     *out = e;
     return SSLBM_OK;
@@ -644,11 +822,16 @@ sslbm_status sslbm_ensemble_run_class(sslbm_ensemble *e, int cls, void *rho, voi
         return SSLBM_OK;
     const bool pairs_ok = pairs_aligned(e, rho, scratch);
     st = ensure_device_tables(e);
-    if (st == SSLBM_OK)
-        st = prepare_run(e, nsteps, pairs_ok);
     if (st != SSLBM_OK)
         return st;
-    return enqueue_class(e, cls, rho, scratch, nsteps, pairs_ok, (hipStream_t)hip_stream);
+    const hipStream_t s = (hipStream_t)hip_stream;
+    if (e->classes[cls].on_chip)
+        return enqueue_on_chip(e, e->classes[cls], rho, nsteps, s);
+    const std::vector<Chain> chain{class_chain(e, cls, nsteps, pairs_ok)};
+    st = prepare_chains(e, chain, nsteps, pairs_ok);
+    if (st != SSLBM_OK)
+        return st;
+    return enqueue_chain(e, chain[0], rho, scratch, nsteps, pairs_ok, s);
 }
 
 sslbm_status sslbm_ensemble_run(sslbm_ensemble *e, void *rho, void *scratch, long long nsteps,
@@ -664,12 +847,13 @@ sslbm_status sslbm_ensemble_run(sslbm_ensemble *e, void *rho, void *scratch, lon
     st = ensure_device_tables(e);
     if (st != SSLBM_OK)
         return st;
-    st = prepare_run(e, nsteps, pairs_ok);
+    const std::vector<Chain> chains = march_chains(e, nsteps, pairs_ok);
+    st = prepare_chains(e, chains, nsteps, pairs_ok);
     if (st != SSLBM_OK)
         return st;
     const hipStream_t user = (hipStream_t)hip_stream;
     if (!(flags & SSLBM_RUN_GRAPH))
-        return enqueue_run(e, rho, scratch, nsteps, pairs_ok, user);
+        return enqueue_run(e, chains, rho, scratch, nsteps, pairs_ok, user);
 
     const GraphKey key{nsteps, rho, scratch};
     auto it = e->graphs.find(key);
@@ -677,7 +861,7 @@ sslbm_status sslbm_ensemble_run(sslbm_ensemble *e, void *rho, void *scratch, lon
         st = hip_status(e, hipStreamBeginCapture(e->stream, hipStreamCaptureModeThreadLocal));
         if (st != SSLBM_OK)
             return st;
-        const sslbm_status run_st = enqueue_run(e, rho, scratch, nsteps, pairs_ok, e->stream);
+        const sslbm_status run_st = enqueue_run(e, chains, rho, scratch, nsteps, pairs_ok, e->stream);
         hipGraph_t graph = nullptr;
         const hipError_t end = hipStreamEndCapture(e->stream, &graph);
         if (run_st != SSLBM_OK) {

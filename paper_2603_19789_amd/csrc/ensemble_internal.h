@@ -21,6 +21,11 @@ struct EnsTile {
 hipError_t launch_ensemble(int dtype, const void *in, void *out, const EnsTile *tiles,
                            int ntiles, const void *insts, int bc, int K, int V, bool diffuse_d,
                            hipStream_t s);
+// One pass of K steps over register tiles with R rows a lane (tile_core.h):
+// each entry is a tile's instance and first output cell (x0, y0).
+hipError_t launch_ensemble_tiles(int dtype, const void *in, void *out, const EnsTile *tiles,
+                                 int ntiles, const void *insts, int bc, int K, int R,
+                                 bool diffuse_d, hipStream_t s);
 // Instances whose five fields fit ENS_LDS_BYTES of LDS (64 x 64 in FP32)
 // run all nsteps steps on chip, one workgroup each: lds_inst is a device
 // array of `count` instance indices; lds_bytes (the largest such instance,

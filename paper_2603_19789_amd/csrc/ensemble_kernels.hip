@@ -3,10 +3,12 @@
 // (instance, strip, rows) from a tile table and runs the same march as the
 // single-grid kernel on that instance's buffer with that instance's
 // coefficients; results are bit for bit those of the single-grid kernel.
+// Ensembles too small for that take register tiles (tile_core.h), as small
+// single grids do.
 #include <hip/hip_runtime.h>
 
 #include "ensemble_internal.h"
-#include "march_core.h"
+#include "tile_core.h"
 
 namespace sslbm {
 
@@ -85,6 +87,68 @@ hipError_t launch_ensemble(int dtype, const void *in, void *out, const EnsTile *
                          : dispatch_ek<double, false, 2>(in, out, tiles, ntiles, insts, bc, K, s);
     return diffuse_d ? dispatch_ek<double, true, 1>(in, out, tiles, ntiles, insts, bc, K, s)
                      : dispatch_ek<double, false, 1>(in, out, tiles, ntiles, insts, bc, K, s);
+}
+
+// ---------------------------------------------------------------------------
+// The register-tile pass (tile_core.h) over many grids: one workgroup per
+// entry of the tile table.
+template <typename T, int R, bool DD>
+__global__ __launch_bounds__(64 * TILE_WAVES) void ensemble_tile_kernel(
+    const T *__restrict__ in, T *__restrict__ out, const EnsTile *__restrict__ tiles,
+    const EnsInstance<T> *__restrict__ insts, int bc, int K) {
+    __shared__ TileEdges<T, DD> edges;
+    const EnsTile t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
+    const EnsInstance<T> m = insts[t.inst];
+    GridDesc g;
+    g.nx = m.nx;
+    g.ny = m.ny;
+    g.plane = (long long)m.nx * m.ny;
+    g.bc = bc;
+    tile_pass<T, R, DD>(in + m.offset, out + m.offset, g, m.k, K, t.x0, t.y0, edges);
+}
+
+template <typename T, int R, bool DD>
+static hipError_t launch_et(const void *in, void *out, const EnsTile *tiles, int ntiles,
+                            const void *insts, int bc, int K, hipStream_t st) {
+    if (K < 1 || K > TILE_MAX_DEPTH || 2 * K >= TILE_WAVES * R)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL((ensemble_tile_kernel<T, R, DD>), dim3((unsigned)ntiles),
+                       dim3(64 * TILE_WAVES), 0, st, static_cast<const T *>(in),
+                       static_cast<T *>(out), tiles, static_cast<const EnsInstance<T> *>(insts),
+                       bc, K);
+    return hipGetLastError();
+}
+
+template <bool DD>
+static hipError_t dispatch_et(int dtype, const void *in, void *out, const EnsTile *tiles,
+                              int ntiles, const void *insts, int bc, int K, int R,
+                              hipStream_t s) {
+    if (dtype == SSLBM_F32) {
+        switch (R) {
+        case 2: return launch_et<float, 2, DD>(in, out, tiles, ntiles, insts, bc, K, s);
+        case 3: return launch_et<float, 3, DD>(in, out, tiles, ntiles, insts, bc, K, s);
+        case 4: return launch_et<float, 4, DD>(in, out, tiles, ntiles, insts, bc, K, s);
+        case 5: return launch_et<float, 5, DD>(in, out, tiles, ntiles, insts, bc, K, s);
+        case 7: return launch_et<float, 7, DD>(in, out, tiles, ntiles, insts, bc, K, s);
+        default: return hipErrorInvalidValue;
+        }
+    }
+    switch (R) {
+    case 1: return launch_et<double, 1, DD>(in, out, tiles, ntiles, insts, bc, K, s);
+    case 2: return launch_et<double, 2, DD>(in, out, tiles, ntiles, insts, bc, K, s);
+    case 3: return launch_et<double, 3, DD>(in, out, tiles, ntiles, insts, bc, K, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_ensemble_tiles(int dtype, const void *in, void *out, const EnsTile *tiles,
+                                 int ntiles, const void *insts, int bc, int K, int R,
+                                 bool diffuse_d, hipStream_t s) {
+    if (ntiles <= 0)
+        return hipSuccess;
+    return diffuse_d
+               ? dispatch_et<true>(dtype, in, out, tiles, ntiles, insts, bc, K, R, s)
+               : dispatch_et<false>(dtype, in, out, tiles, ntiles, insts, bc, K, R, s);
 }
 
 // ---------------------------------------------------------------------------

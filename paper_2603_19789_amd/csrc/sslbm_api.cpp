@@ -98,7 +98,8 @@ bool automatic(const sslbm_launch &r) {
 sslbm::TilePlan run_tiles(const sslbm_ctx *c, long long nsteps) {
     if (!automatic(c->launch))
         return sslbm::TilePlan();
-    return sslbm::tile_plan(c->dtype, &c->nx, &c->ny, 1, nsteps);
+    const sslbm::GridSize size{c->nx, c->ny, 1};
+    return sslbm::tile_plan(c->dtype, &size, 1, nsteps);
 }
 
 // March shape of a pass: requested fields, automatic ones filled in.
@@ -371,7 +372,8 @@ sslbm_status sslbm_tune(sslbm_ctx *c, const void *rho, void *scratch, void *hip_
     };
     // Rows under twice the depth pay only on grids that leave SIMDs idle, the
     // ones that the tiles are for; there the tiles are a candidate too.
-    const sslbm::TilePlan tiles = sslbm::tile_plan(c->dtype, &c->nx, &c->ny, 1, 1000);
+    const sslbm::GridSize size{c->nx, c->ny, 1};
+    const sslbm::TilePlan tiles = sslbm::tile_plan(c->dtype, &size, 1, 1000);
     for (int V = 1; V <= (pairs_ok ? 2 : 1) && st == SSLBM_OK; ++V) {
         for (int K = 1; K <= sslbm::march_max_depth(c->dtype, V) && st == SSLBM_OK; ++K) {
             const int cands[] = {0, 1, 2, 4, 8, 16, 32, 64, 128};

@@ -78,15 +78,21 @@ int strip_width(int K, int cols_per_lane);
 int march_resident_waves(int dtype, int K, int cols_per_lane, bool diffuse_d);
 
 // ---- register tiles (tile_kernels.hip) -----------------------------------
+// Wavefronts of a tile's workgroup: a tile has 64 columns x TILE_WAVES R rows.
+constexpr int TILE_WAVES = 16;
 // Most steps a tile takes in one pass (its halo leaves 32 of 64 columns).
 constexpr int TILE_MAX_DEPTH = 16;
-// Tile height (rows a lane) and steps per pass for a run of nsteps on `count`
-// grids that advance together; rows = 0: the grids are too large, march.
+// Tile height (rows a lane) and steps per pass for a run of nsteps on grids of
+// n sizes that advance together; rows = 0: the grids are too large, march.
 struct TilePlan {
     int rows = 0;
     int depth = 0;
 };
-TilePlan tile_plan(int dtype, const int *nx, const int *ny, int count, long long nsteps);
+struct GridSize {
+    int nx, ny;
+    int count;  // grids of this size
+};
+TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps);
 long long tile_count(int nx, int ny, int R, int K);
 // K steps in -> out (no overlap) with R rows a lane.
 hipError_t launch_tile(int dtype, const void *in, void *out, const GridDesc &g, const StepCoef &k,

@@ -25,8 +25,6 @@
 
 namespace sslbm {
 
-constexpr int TILE_WAVES = 16;
-
 template <typename T, bool DD>
 struct TileEdges {
     T row[2][TILE_WAVES][2][DD ? 5 : 4][64];  // [step parity][wavefront][first, last row]

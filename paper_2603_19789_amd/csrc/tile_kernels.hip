@@ -54,27 +54,27 @@ double pass_us(int dtype, int R, int K, long long tiles, int cus) {
 
 }  // namespace
 
-TilePlan tile_plan(int dtype, const int *nx, const int *ny, int count, long long nsteps) {
+TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps) {
     TilePlan best;
     // Up to where the march has enough rows for every SIMD, it waits for
     // memory (FP32 1152^2: 3.64 against 3.83 us a step, 1280^2 4.27 against
     // 4.2; FP64 640^2: 2.55 against 2.80, 704^2 3.58 against 3.21).
     const long long most = dtype == SSLBM_F32 ? 1400000 : 450000;
     long long cells = 0;
-    for (int i = 0; i < count; ++i)
-        cells += (long long)nx[i] * ny[i];
+    for (int i = 0; i < n; ++i)
+        cells += (long long)sizes[i].nx * sizes[i].ny * sizes[i].count;
     if (cells > most || nsteps <= 0)
         return best;
     const int cus = compute_units();
     constexpr int F32_ROWS[] = {2, 3, 4, 5, 7}, F64_ROWS[] = {1, 2, 3};
     const int *rows = dtype == SSLBM_F32 ? F32_ROWS : F64_ROWS;
-    const int shapes = dtype == SSLBM_F32 ? 5 : 3;
+    const int heights = dtype == SSLBM_F32 ? 5 : 3;
     double best_us = 0.0;
-    for (int j = 0; j < shapes; ++j)
+    for (int j = 0; j < heights; ++j)
         for (int K = 1; K <= TILE_MAX_DEPTH && 2 * K < TILE_WAVES * rows[j]; ++K) {
             long long tiles = 0;
-            for (int i = 0; i < count; ++i)
-                tiles += tile_count(nx[i], ny[i], rows[j], K);
+            for (int i = 0; i < n; ++i)
+                tiles += tile_count(sizes[i].nx, sizes[i].ny, rows[j], K) * sizes[i].count;
             if (tiles > 0x7fffffffll)
                 continue;
             const PassPlan p = plan_passes(nsteps, K);
