@@ -43,9 +43,11 @@ FLAGS = [
 
 # Per-source additions. The MFMA kernels keep their accumulators in ordinary
 # VGPRs: with the accumulation registers, this compiler copied the running
-# sums of the two-deep convolution pipeline back and forth every step.
+# sums of the two-deep convolution pipeline back and forth every step (and the
+# generic model's compartment sums at every node).
 EXTRA_FLAGS = {
     "surrogate_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "model_kernels_inst.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

@@ -178,8 +178,11 @@ sslbm_status sslbm_model_run(sslbm_model *m, void *rho, void *scratch, long long
     const hipStream_t s = (hipStream_t)hip_stream;
     const int K = resolved_blocking(m);
     void *src = rho, *dst = scratch;
-    for (long long n = 0; n < nsteps;) {
-        const int k = nsteps - n < K ? (int)(nsteps - n) : K;
+    // an even number of passes where every one keeps a step, so that the
+    // result ends in rho
+    const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, K);
+    for (long long i = 0; i < plan.count; ++i) {
+        const int k = plan.steps(i);
         const sslbm_status st = hip_status(m, sslbm::launch_model(m->dtype, m->lattice, src, dst,
                                                          grid_of(m), m->coef, m->table, k, s));
         if (st != SSLBM_OK)
@@ -187,7 +190,6 @@ sslbm_status sslbm_model_run(sslbm_model *m, void *rho, void *scratch, long long
         void *tmp = src;
         src = dst;
         dst = tmp;
-        n += k;
     }
     if (src != rho)
         return hip_status(m, hipMemcpyAsync(rho, src, bytes, hipMemcpyDeviceToDevice, s));

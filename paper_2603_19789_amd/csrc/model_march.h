@@ -17,9 +17,10 @@
 // Sources. Transition r moves rate_r dt C[src] (C[cat] if cat >= 0)
 // (/ N if frequency-dependent, 0 where N <= 0) from src to dst (dst < 0:
 // out of the system); N sums the compartments flagged as counted. The table
-// is the same for every node and sits in LDS; each lane also keeps its
-// compartment vector in LDS slots, so a lookup by table index is a single
-// LDS access rather than a select over all compartments.
+// is the same for every node. Each lane keeps its compartment vector in LDS
+// slots, so a lookup by table index is a single LDS access rather than a
+// select over all compartments. FP32 holds the rest of the table in registers
+// and adds the flows on the matrix cores (FlowTable); FP64 reads it from LDS.
 //
 // Traversal: the y-march of the SEIRD pass kernel with K steps per pass
 // (one wavefront per strip of 64 - 2K output columns plus K halo columns
@@ -41,6 +42,7 @@ namespace sslbm {
 namespace model_detail {
 
 constexpr int MODEL_GROUP = 4;  // transitions looked up together (divides MODEL_MAX_T)
+constexpr int FEW_T = 8;        // transitions of the FP32 kernels for short tables
 
 template <int K>
 struct ModelStrip {
@@ -87,12 +89,41 @@ struct LaneLds {
     T *vals;
 };
 
+// FP32: the stoichiometry as matrix operands. A transition adds its flow times
+// a column of M coefficients, the same for every node, to a node's M values:
+// an outer product, which V_MFMA_F32_4X4X1 (16 blocks of 4 x 4) takes four
+// nodes a block. Its B operand and its four results lie in the node's own
+// lane, so a lane's flow and accumulators need no shuffle; the A operand holds
+// coefficients 4h + (lane mod 4) of transition r. Each result is one fused
+// multiply-add, as fma().
+//
+// The tables are the same for every node, so a lane also keeps the LDS
+// addresses of its lookups (source, catalyst, and 1 / N or 1): unpacking
+// indices on the scalar unit for every node cost as many issue slots as the
+// arithmetic.
+//
+// What bounds the pass: vector issue, about 137 instructions a node and level
+// on D2Q9 with eight transitions (16 of them matrix ones), and the wait for
+// the lookups. 2048^2, six compartments, seven transitions, three steps per
+// pass: 32.0 -> 27.0 us a step on D2Q9, 30.3 -> 22.5 on D2Q5. On the way: the
+// table in LDS 32.0 (its broadcasts bound the pass); coefficients in matrix
+// operands and packed indices 29.0; address-free LDS reads (M0) 30.2 and eight
+// lookups in flight instead of four 30.6, both slower.
+template <int M, int NT>
+struct FlowTable {
+    static constexpr int H = (M + 3) / 4;
+    float a[NT][H];
+    const float *src[NT], *cat[NT], *per[NT];
+};
+using Acc4 = float __attribute__((ext_vector_type(4)));
+
 // Level L (1..K) at phase P: the row of level L from three rows of level
 // L-1 (slots P-L-1, P-L, P-L+1 mod 4), into slot P-L of level L, or to HBM
 // for L = K.
-template <typename T, int Q, int M, int K, int P, int L>
+template <typename T, int Q, int M, int K, int NT, int P, int L>
 __device__ __forceinline__ void model_level(ModelRows<T, K> &st, const ModelArgs<T> &a,
-                                            const ModelCoef<T> &k, const LaneLds<T> &lds, int t) {
+                                            const ModelCoef<T> &k, const LaneLds<T> &lds,
+                                            const FlowTable<M, NT> &ft, int t) {
     constexpr int su = ((P - L - 1) % RING + RING) % RING;
     constexpr int sm = ((P - L) % RING + RING) % RING;
     constexpr int sd = ((P - L + 1) % RING + RING) % RING;
@@ -124,29 +155,64 @@ __device__ __forceinline__ void model_level(ModelRows<T, K> &st, const ModelArgs
     // 1 / N once per node (0 where N is not a positive normal number: no
     // frequency-dependent flow)
     const T inv_total = recip_or_zero(total);
-    // MODEL_GROUP transitions at a time: their lookups are issued together,
-    // so a group costs one LDS latency; increments go straight into the
-    // output registers through the stoichiometry rows (rate dt (delta_dst -
-    // delta_src), uniform LDS broadcasts). The table is padded with
-    // zero-rate transitions to a multiple of MODEL_GROUP.
-    for (int r0 = 0; r0 < k.ntrans; r0 += MODEL_GROUP) {
-        int4 d[MODEL_GROUP];
-        T sv[MODEL_GROUP], cv[MODEL_GROUP];
+    if constexpr (sizeof(T) == 4) {
+        // LDS serves nothing but the lookups (with the whole table in LDS, its
+        // broadcasts bound the pass). Groups past the last transition are
+        // skipped by a wavefront-uniform branch; the table is padded with
+        // zero-rate transitions to a multiple of MODEL_GROUP.
+        lds.vals[(M + 1) * 64] = inv_total;
+        Acc4 acc[2];
 #pragma unroll
-        for (int j = 0; j < MODEL_GROUP; ++j)
-            d[j] = lds.itab[r0 + j];  // src, catalyst slot, destination, frequency
+        for (int h = 0; h < FlowTable<M, NT>::H; ++h)
+            acc[h] = Acc4{out[4 * h], out[4 * h + 1], out[4 * h + 2], out[4 * h + 3]};
 #pragma unroll
-        for (int j = 0; j < MODEL_GROUP; ++j) {
-            sv[j] = lds.vals[d[j].x * 64];
-            cv[j] = lds.vals[d[j].y * 64];
+        for (int r0 = 0; r0 < NT; r0 += MODEL_GROUP) {
+            if (r0 >= k.ntrans)
+                break;
+            float sv[MODEL_GROUP], cv[MODEL_GROUP], pv[MODEL_GROUP];
+#pragma unroll
+            for (int j = 0; j < MODEL_GROUP; ++j) {
+                sv[j] = *ft.src[r0 + j];
+                cv[j] = *ft.cat[r0 + j];
+                pv[j] = *ft.per[r0 + j];
+            }
+#pragma unroll
+            for (int j = 0; j < MODEL_GROUP; ++j) {
+                const float flow = sv[j] * cv[j] * pv[j];
+#pragma unroll
+                for (int h = 0; h < FlowTable<M, NT>::H; ++h)
+                    acc[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(ft.a[r0 + j][h], flow, acc[h], 0,
+                                                                0, 0);
+            }
         }
 #pragma unroll
-        for (int j = 0; j < MODEL_GROUP; ++j) {
-            const T flow = sv[j] * cv[j] * (d[j].w ? inv_total : T(1));
-            const T *row = lds.stoich + (r0 + j) * MODEL_MAX_C;
+        for (int c = 0; c < M; ++c)
+            out[c] = acc[c / 4][c % 4];
+    } else {
+        // MODEL_GROUP transitions at a time: their lookups are issued together,
+        // so a group costs one LDS latency; increments go straight into the
+        // output registers through the stoichiometry rows (rate dt (delta_dst
+        // - delta_src), uniform LDS broadcasts). The table is padded with
+        // zero-rate transitions to a multiple of MODEL_GROUP.
+        for (int r0 = 0; r0 < k.ntrans; r0 += MODEL_GROUP) {
+            int4 d[MODEL_GROUP];
+            T sv[MODEL_GROUP], cv[MODEL_GROUP];
 #pragma unroll
-            for (int c = 0; c < M; ++c)
-                out[c] = fma(row[c], flow, out[c]);
+            for (int j = 0; j < MODEL_GROUP; ++j)
+                d[j] = lds.itab[r0 + j];  // src, catalyst slot, destination, frequency
+#pragma unroll
+            for (int j = 0; j < MODEL_GROUP; ++j) {
+                sv[j] = lds.vals[d[j].x * 64];
+                cv[j] = lds.vals[d[j].y * 64];
+            }
+#pragma unroll
+            for (int j = 0; j < MODEL_GROUP; ++j) {
+                const T flow = sv[j] * cv[j] * (d[j].w ? inv_total : T(1));
+                const T *row = lds.stoich + (r0 + j) * MODEL_MAX_C;
+#pragma unroll
+                for (int c = 0; c < M; ++c)
+                    out[c] = fma(row[c], flow, out[c]);
+            }
         }
     }
     if constexpr (L < K) {
@@ -161,55 +227,73 @@ __device__ __forceinline__ void model_level(ModelRows<T, K> &st, const ModelArgs
     }
 }
 
-template <typename T, int Q, int M, int K, int P, int L, int LMAX>
+template <typename T, int Q, int M, int K, int NT, int P, int L, int LMAX>
 __device__ __forceinline__ void model_levels(ModelRows<T, K> &st, const ModelArgs<T> &a,
                                              const ModelCoef<T> &k, const LaneLds<T> &lds,
-                                             int t) {
+                                             const FlowTable<M, NT> &ft, int t) {
     if constexpr (L <= LMAX) {
-        model_level<T, Q, M, K, P, L>(st, a, k, lds, t);
-        model_levels<T, Q, M, K, P, L + 1, LMAX>(st, a, k, lds, t);
+        model_level<T, Q, M, K, NT, P, L>(st, a, k, lds, ft, t);
+        model_levels<T, Q, M, K, NT, P, L + 1, LMAX>(st, a, k, lds, ft, t);
     }
 }
 
 // Warm-up rows t = TC < 2K: fetch row t + 1, then the levels that already
 // have three rows below them (l <= t/2). Nothing is stored yet.
-template <typename T, int Q, int M, int K, int TC>
+template <typename T, int Q, int M, int K, int NT, int TC>
 __device__ __forceinline__ void model_warm_up(ModelRows<T, K> &st, const ModelArgs<T> &a,
-                                              const ModelCoef<T> &k, const LaneLds<T> &lds) {
+                                              const ModelCoef<T> &k, const LaneLds<T> &lds,
+                                              const FlowTable<M, NT> &ft) {
     if constexpr (TC < 2 * K) {
         fetch_rows<T, K, M, (TC + 1) % RING>(st, a, TC + 1);
-        model_levels<T, Q, M, K, TC % RING, 1, TC / 2>(st, a, k, lds, TC);
-        model_warm_up<T, Q, M, K, TC + 1>(st, a, k, lds);
+        model_levels<T, Q, M, K, NT, TC % RING, 1, TC / 2>(st, a, k, lds, ft, TC);
+        model_warm_up<T, Q, M, K, NT, TC + 1>(st, a, k, lds, ft);
     }
 }
 
 // Steady-state row t (phase P): fetch row t + 1, all K levels, one output row.
-template <typename T, int Q, int M, int K, int P>
+template <typename T, int Q, int M, int K, int NT, int P>
 __device__ __forceinline__ void model_steady(ModelRows<T, K> &st, const ModelArgs<T> &a,
                                              const ModelCoef<T> &k, const LaneLds<T> &lds,
-                                             int t) {
+                                             const FlowTable<M, NT> &ft, int t) {
     fetch_rows<T, K, M, (P + 1) % RING>(st, a, t + 1);
-    model_levels<T, Q, M, K, P, 1, K>(st, a, k, lds, t);
+    model_levels<T, Q, M, K, NT, P, 1, K>(st, a, k, lds, ft, t);
 }
 
-template <typename T, int Q, int M, int K>
+template <typename T, int Q, int M, int K, int NT>
 __global__ __launch_bounds__(BLOCK_THREADS) void model_kernel(const T *__restrict__ in,
                                                               T *__restrict__ out, GridDesc g,
                                                               ModelCoef<T> k,
                                                               const T *__restrict__ table,
                                                               int strips, int chunks, int rows) {
-    // the transition table, copied to LDS by the whole workgroup before any
-    // wavefront may leave; per-lane slots for the source lookups
-    __shared__ int4 itab[MODEL_MAX_T];
-    __shared__ T stoich[MODEL_MAX_T * MODEL_MAX_C];
-    __shared__ T vals[WAVES_PER_BLOCK][(MODEL_MAX_C + 1) * 64];
-    if (threadIdx.x < (unsigned)MODEL_MAX_T) {
-        const int *row = reinterpret_cast<const int *>(table) + 4 * threadIdx.x;
-        itab[threadIdx.x] = make_int4(row[0], row[1], row[2], row[3]);
+    // per-lane slots for the source lookups; FP64 also copies the transition
+    // table to LDS, by the whole workgroup before any wavefront may leave
+    constexpr bool TABLE = sizeof(T) == 8;
+    __shared__ int4 itab[TABLE ? MODEL_MAX_T : 1];
+    __shared__ T stoich[TABLE ? MODEL_MAX_T * MODEL_MAX_C : 1];
+    __shared__ T vals[WAVES_PER_BLOCK][(MODEL_MAX_C + 2) * 64];
+    const T *coef = reinterpret_cast<const T *>(reinterpret_cast<const int *>(table) +
+                                                4 * MODEL_MAX_T);
+    FlowTable<M, NT> ft;
+    if constexpr (TABLE) {
+        if (threadIdx.x < (unsigned)MODEL_MAX_T) {
+            const int *row = reinterpret_cast<const int *>(table) + 4 * threadIdx.x;
+            itab[threadIdx.x] = make_int4(row[0], row[1], row[2], row[3]);
+        }
+        if (threadIdx.x < (unsigned)(MODEL_MAX_T * MODEL_MAX_C))
+            stoich[threadIdx.x] = coef[threadIdx.x];
+    } else {
+        const int *row = reinterpret_cast<const int *>(table);
+        const float *mine = &vals[threadIdx.x >> 6][threadIdx.x & 63];
+#pragma unroll
+        for (int r = 0; r < NT; ++r) {
+#pragma unroll
+            for (int h = 0; h < FlowTable<M, NT>::H; ++h)
+                ft.a[r][h] = coef[r * MODEL_MAX_C + 4 * h + (threadIdx.x & 3)];
+            ft.src[r] = mine + row[4 * r] * 64;
+            ft.cat[r] = mine + row[4 * r + 1] * 64;
+            ft.per[r] = mine + (row[4 * r + 3] ? M + 1 : M) * 64;
+        }
     }
-    if (threadIdx.x < (unsigned)(MODEL_MAX_T * MODEL_MAX_C))
-        stoich[threadIdx.x] = reinterpret_cast<const T *>(reinterpret_cast<const int *>(table) +
-                                                          4 * MODEL_MAX_T)[threadIdx.x];
     {
         const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
         vals[w][M * 64 + l] = T(1);
@@ -252,23 +336,23 @@ __global__ __launch_bounds__(BLOCK_THREADS) void model_kernel(const T *__restric
                 st.ring[l][s][c] = T(0);
     // rows 0 .. 2K-1 fill the levels; from row 2K on every row yields output
     fetch_rows<T, K, M, 0>(st, a, 0);
-    model_warm_up<T, Q, M, K, 0>(st, a, k, lds);
+    model_warm_up<T, Q, M, K, NT, 0>(st, a, k, lds, ft);
     constexpr int P0 = (2 * K) % RING;
     int t = 2 * K;
     for (; t + RING <= a.tend; t += RING) {
-        model_steady<T, Q, M, K, P0>(st, a, k, lds, t);
-        model_steady<T, Q, M, K, (P0 + 1) % RING>(st, a, k, lds, t + 1);
-        model_steady<T, Q, M, K, (P0 + 2) % RING>(st, a, k, lds, t + 2);
-        model_steady<T, Q, M, K, (P0 + 3) % RING>(st, a, k, lds, t + 3);
+        model_steady<T, Q, M, K, NT, P0>(st, a, k, lds, ft, t);
+        model_steady<T, Q, M, K, NT, (P0 + 1) % RING>(st, a, k, lds, ft, t + 1);
+        model_steady<T, Q, M, K, NT, (P0 + 2) % RING>(st, a, k, lds, ft, t + 2);
+        model_steady<T, Q, M, K, NT, (P0 + 3) % RING>(st, a, k, lds, ft, t + 3);
     }
     // last partial group of rows, nested so that no older ring value stays
     // live through the loop for a tail row that might read it
     if (t < a.tend) {
-        model_steady<T, Q, M, K, P0>(st, a, k, lds, t);
+        model_steady<T, Q, M, K, NT, P0>(st, a, k, lds, ft, t);
         if (t + 1 < a.tend) {
-            model_steady<T, Q, M, K, (P0 + 1) % RING>(st, a, k, lds, t + 1);
+            model_steady<T, Q, M, K, NT, (P0 + 1) % RING>(st, a, k, lds, ft, t + 1);
             if (t + 2 < a.tend)
-                model_steady<T, Q, M, K, (P0 + 2) % RING>(st, a, k, lds, t + 2);
+                model_steady<T, Q, M, K, NT, (P0 + 2) % RING>(st, a, k, lds, ft, t + 2);
         }
     }
 }
@@ -276,7 +360,7 @@ __global__ __launch_bounds__(BLOCK_THREADS) void model_kernel(const T *__restric
 // Wavefronts of model_kernel<T, Q, M, K> that fit on one SIMD at once (512
 // VGPRs per lane, allocated in granules of 8), from the built kernel's
 // register count; queried once per device.
-template <typename T, int Q, int M, int K>
+template <typename T, int Q, int M, int K, int NT>
 int resident_waves_per_simd() {
     static int cached[16] = {};
     int dev = 0;
@@ -287,7 +371,7 @@ int resident_waves_per_simd() {
     if (cached[dev])
         return cached[dev];
     hipFuncAttributes attr;
-    if (hipFuncGetAttributes(&attr, (const void *)model_kernel<T, Q, M, K>) != hipSuccess) {
+    if (hipFuncGetAttributes(&attr, (const void *)model_kernel<T, Q, M, K, NT>) != hipSuccess) {
         (void)hipGetLastError();
         return 1;
     }
@@ -298,28 +382,39 @@ int resident_waves_per_simd() {
     return per;
 }
 
-template <typename T, int Q, int M, int K>
+template <typename T, int Q, int M, int K, int NT>
 hipError_t launch_mk(const void *in, void *out, const GridDesc &g, const ModelCoef<T> &k,
                      const void *table, hipStream_t s) {
-    const ModelShape sh = model_shape(g.nx, g.ny, K, resident_waves_per_simd<T, Q, M, K>());
+    const ModelShape sh = model_shape(g.nx, g.ny, K, resident_waves_per_simd<T, Q, M, K, NT>());
     const int waves = sh.strips * sh.chunks;
-    hipLaunchKernelGGL((model_kernel<T, Q, M, K>), dim3((unsigned)((waves + 3) / 4)),
+    hipLaunchKernelGGL((model_kernel<T, Q, M, K, NT>), dim3((unsigned)((waves + 3) / 4)),
                        dim3(BLOCK_THREADS), 0, s, static_cast<const T *>(in),
                        static_cast<T *>(out), g, k, static_cast<const T *>(table), sh.strips,
                        sh.chunks, sh.rows);
     return hipGetLastError();
 }
 
+template <typename T, int Q, int M, int NT>
+hipError_t launch_n(const void *in, void *out, const GridDesc &g, const ModelCoef<T> &k,
+                    const void *table, int K, hipStream_t s) {
+    switch (K) {
+    case 1: return launch_mk<T, Q, M, 1, NT>(in, out, g, k, table, s);
+    case 2: return launch_mk<T, Q, M, 2, NT>(in, out, g, k, table, s);
+    case 3: return launch_mk<T, Q, M, 3, NT>(in, out, g, k, table, s);
+    case 4: return launch_mk<T, Q, M, 4, NT>(in, out, g, k, table, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// FP32 kernels hold the tables of NT transitions in registers: short tables
+// (up to 8) have their own, which fit four wavefronts a SIMD at three steps.
 template <typename T, int Q, int M>
 hipError_t launch_m(const void *in, void *out, const GridDesc &g, const ModelCoef<T> &k,
                     const void *table, int K, hipStream_t s) {
-    switch (K) {
-    case 1: return launch_mk<T, Q, M, 1>(in, out, g, k, table, s);
-    case 2: return launch_mk<T, Q, M, 2>(in, out, g, k, table, s);
-    case 3: return launch_mk<T, Q, M, 3>(in, out, g, k, table, s);
-    case 4: return launch_mk<T, Q, M, 4>(in, out, g, k, table, s);
-    default: return hipErrorInvalidValue;
-    }
+    if constexpr (sizeof(T) == 4)
+        if (k.ntrans <= FEW_T)
+            return launch_n<T, Q, M, FEW_T>(in, out, g, k, table, K, s);
+    return launch_n<T, Q, M, MODEL_MAX_T>(in, out, g, k, table, K, s);
 }
 
 template <typename T, int Q>
