@@ -302,12 +302,11 @@ void sslbm_destroy(sslbm_ctx *c);
  *       sslbm_run_checkpointed stores; -1 for nsteps < 0 or every < 1.
  *   sslbm_run_checkpointed: as sslbm_run (result in rho, scratch clobbered),
  *       and stores the state at steps 0, every, 2 every, ... into
- *       checkpoints, a device buffer of sslbm_checkpoint_count states. For
- *       every up to the deepest single pass of the dtype (5 in FP64, 8 in
- *       FP32) each segment is one pass written straight into the next
- *       checkpoint (scratch unused), two segments per pass when every
- *       = 2; the reverse sweep then recomputes nothing, at the cost of
- *       nsteps / 2 stored states (1024^2 FP64 x 2000 steps: 42 GB).
+ *       checkpoints, a device buffer of sslbm_checkpoint_count states. Each
+ *       segment runs straight into the next checkpoint, and every = 2 takes
+ *       two segments per pass; the reverse sweep then recomputes nothing, at
+ *       the cost of nsteps / 2 stored states (1024^2 FP64 x 2000 steps:
+ *       42 GB).
  *   sslbm_adjoint_workspace_bytes: bytes of device workspace the reverse
  *       sweep needs for this context and checkpoint interval (about
  *       every / 2 + 1 states plus 128 bytes per wavefront of the adjoint

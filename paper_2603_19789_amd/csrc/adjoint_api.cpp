@@ -184,42 +184,28 @@ sslbm_status sslbm_run_checkpointed(sslbm_ctx *c, void *rho, void *scratch, long
     const hipStream_t s = (hipStream_t)hip_stream;
     if (count == 0)
         return SSLBM_OK;
-    if (every <= sslbm::march_max_depth(c->dtype, 1)) {
-        // One pass per segment, written straight into the next checkpoint
-        // (the last one into rho): one copy in all, no ping-pong through
-        // scratch; checkpoints every 2 steps take two segments per pass. The
-        // pass kernel gives the same bits at every depth.
-        char *cp = static_cast<char *>(checkpoints);
-        sslbm_status st = hip_status(c, hipMemcpyAsync(cp, rho, bytes, hipMemcpyDeviceToDevice, s));
-        if (st != SSLBM_OK)
-            return st;
-        auto slot = [&](long long k) -> void * {
-            return k < count ? static_cast<void *>(cp + (size_t)k * bytes) : rho;
-        };
-        for (long long k = 0; k < count;) {
-            const long long n = nsteps - k * every < every ? nsteps - k * every : every;
-            if (every == 2 && n == 2 && k + 1 < count && nsteps - (k + 1) * every >= 2) {
-                // two segments in one pass of 4 steps, the state after 2
-                // steps written on the way
-                st = sslbm::run_pass_mid2(c, slot(k), slot(k + 1), slot(k + 2), s);
-                k += 2;
-            } else {
-                st = sslbm::run_pass(c, slot(k), slot(k + 1), (int)n, s);
-                k += 1;
-            }
-            if (st != SSLBM_OK)
-                return st;
-        }
-        return SSLBM_OK;
-    }
-    for (long long k = 0; k < count; ++k) {
-        char *slot = static_cast<char *>(checkpoints) + (size_t)k * bytes;
-        sslbm_status st =
-            hip_status(c, hipMemcpyAsync(slot, rho, bytes, hipMemcpyDeviceToDevice, s));
-        if (st != SSLBM_OK)
-            return st;
+    // Every segment runs from its checkpoint straight into the next one (the
+    // last one into rho), through scratch and rho: one copy in all, and no
+    // pass more to make their count even. Checkpoints every 2 steps take two
+    // segments per pass. Every pass gives the same bits at every depth.
+    char *cp = static_cast<char *>(checkpoints);
+    sslbm_status st = hip_status(c, hipMemcpyAsync(cp, rho, bytes, hipMemcpyDeviceToDevice, s));
+    if (st != SSLBM_OK)
+        return st;
+    auto slot = [&](long long k) -> void * {
+        return k < count ? static_cast<void *>(cp + (size_t)k * bytes) : rho;
+    };
+    for (long long k = 0; k < count;) {
         const long long n = nsteps - k * every < every ? nsteps - k * every : every;
-        st = sslbm_run(c, rho, scratch, n, hip_stream);
+        if (every == 2 && n == 2 && k + 1 < count && nsteps - (k + 1) * every >= 2) {
+            // two segments in one pass of 4 steps, the state after 2 steps
+            // written on the way
+            st = sslbm::run_pass_mid2(c, slot(k), slot(k + 1), slot(k + 2), s);
+            k += 2;
+        } else {
+            st = sslbm::run_segment(c, slot(k), slot(k + 1), scratch, rho, n, s);
+            k += 1;
+        }
         if (st != SSLBM_OK)
             return st;
     }

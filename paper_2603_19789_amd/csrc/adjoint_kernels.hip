@@ -438,14 +438,16 @@ __global__ __launch_bounds__(256) void zero_kernel(double *__restrict__ p, long 
         p[e] = 0.0;
 }
 
-// Sum of the slots in a fixed order (slot-strided per thread, then a fixed
-// tree), scaled into the nine parameter gradients and added to grad. Each
-// thread reads whole slots, so its loads are independent and contiguous.
-constexpr int FINISH_THREADS = 512;
+// Sum of the slots in a fixed order (slot-strided per thread, then over the
+// lanes of a wavefront, then over the wavefronts), scaled into the nine
+// parameter gradients and added to grad. Each thread reads whole slots, so its
+// loads are independent and contiguous. Lane sums by shuffles leave one barrier
+// (nine, with a tree in LDS, cost most of the 11 us the launch took).
+constexpr int FINISH_THREADS = 512, FINISH_WAVES = FINISH_THREADS / 64;
 
 __global__ __launch_bounds__(FINISH_THREADS) void adjoint_finish_kernel(
     const double *__restrict__ partials, int slots, AdjFactors f, double *__restrict__ grad) {
-    __shared__ double part[ADJ_SUMS][FINISH_THREADS];
+    __shared__ double part[FINISH_WAVES][ADJ_SUMS];
     const int tid = threadIdx.x;
     double s[ADJ_SUMS];
 #pragma unroll
@@ -459,24 +461,28 @@ __global__ __launch_bounds__(FINISH_THREADS) void adjoint_finish_kernel(
     }
 #pragma unroll
     for (int j = 0; j < ADJ_SUMS; ++j)
-        part[j][tid] = s[j];
-    __syncthreads();
-    for (int h = FINISH_THREADS / 2; h >= 1; h >>= 1) {
-        if (tid < h) {
+        s[j] = wave_sum(s[j]);
+    if ((tid & 63) == 0) {
 #pragma unroll
-            for (int j = 0; j < ADJ_SUMS; ++j)
-                part[j][tid] += part[j][tid + h];
-        }
-        __syncthreads();
+        for (int j = 0; j < ADJ_SUMS; ++j)
+            part[tid >> 6][j] = s[j];
     }
+    __syncthreads();
+    auto sum = [&](int j) {
+        double v = part[0][j];
+#pragma unroll
+        for (int w = 1; w < FINISH_WAVES; ++w)
+            v += part[w][j];
+        return v;
+    };
     if (tid < 9) {
         double v;
         switch (tid) {
-        case 0: v = f.dt * part[0][0]; break;
-        case 1: v = f.dt * part[1][0]; break;
-        case 2: v = f.dt * ((1.0 - f.phi) * part[3][0] + f.phi * part[4][0] - part[2][0]); break;
-        case 3: v = f.gamma_dt * (part[4][0] - part[3][0]); break;
-        default: v = f.dt_dx2 * part[5 + (tid - 4)][0]; break;
+        case 0: v = f.dt * sum(0); break;
+        case 1: v = f.dt * sum(1); break;
+        case 2: v = f.dt * ((1.0 - f.phi) * sum(3) + f.phi * sum(4) - sum(2)); break;
+        case 3: v = f.gamma_dt * (sum(4) - sum(3)); break;
+        default: v = f.dt_dx2 * sum(5 + (tid - 4)); break;
         }
         grad[tid] += v;
     }
@@ -497,10 +503,16 @@ hipError_t launch_t(const void *rho, const void *lam, void *out, const GridDesc 
 
 }  // namespace
 
+// Least rows of a chunk. Small grids leave SIMDs idle, and a launch lasts as
+// long as one march with its halo rows. With 2 instead of 8 the reverse sweep
+// (recomputation included) of 128^2 takes 5.5 instead of 9.0 us a step in FP64
+// and 4.9 instead of 7.9 in FP32; 256^2 FP64 6.0 instead of 9.3.
+constexpr int ADJ_MIN_ROWS = 2;
+
 AdjShape adjoint_shape(int nx, int ny) {
     AdjShape s;
     s.strips = (nx + ADJ_WU - 1) / ADJ_WU;
-    // The shortest chunks (at least 8 rows) for which the grid fits in one
+    // The shortest chunks (of at least ADJ_MIN_ROWS) for which the grid fits in one
     // workgroup of 4 wavefronts per CU of the 256 of an MI355X: measured at
     // 1024 x 1024 in FP64, one wavefront per SIMD on long chunks beats more
     // wavefronts on short ones (25.5 us per step at 24 rows, 31 us at 16 rows
@@ -511,8 +523,8 @@ AdjShape adjoint_shape(int nx, int ny) {
     if (chunks < 1)
         chunks = 1;
     long long rows = (ny + chunks - 1) / chunks;
-    if (rows < 8)
-        rows = 8;
+    if (rows < ADJ_MIN_ROWS)
+        rows = ADJ_MIN_ROWS;
     if (rows > ny)
         rows = ny;
     s.rows = (int)rows;
@@ -533,15 +545,14 @@ hipError_t launch_adjoint(int dtype, const void *rho, const void *lam, void *out
 AdjShape adjoint2_shape(int nx, int ny) {
     AdjShape s;
     s.strips = (nx + F_WU - 1) / F_WU;
-    // as adjoint_shape: one workgroup of four wavefronts per CU, chunks of
-    // at least 8 rows
+    // as adjoint_shape
     const long long target = 256 * WAVES_PER_BLOCK;
     long long chunks = target / s.strips;
     if (chunks < 1)
         chunks = 1;
     long long rows = (ny + chunks - 1) / chunks;
-    if (rows < 8)
-        rows = 8;
+    if (rows < ADJ_MIN_ROWS)
+        rows = ADJ_MIN_ROWS;
     if (rows > ny)
         rows = ny;
     s.rows = (int)rows;

@@ -44,8 +44,14 @@ sslbm_status hip_status(sslbm_ctx *c, hipError_t e) {
 
 // Steps per pass and columns per lane when the caller has not chosen: the
 // fastest shapes measured on MI355X for large grids (the pass turns from
-// HBM-bound to ALU-bound around there).
-int auto_depth(const sslbm_ctx *c) { return c->dtype == SSLBM_F32 ? 6 : 5; }
+// HBM-bound to ALU-bound around there). FP64 with a diffusing D takes one step
+// less: its five-step kernel spills (172 B of scratch per lane; 1024^2: 6.8 us
+// a step against 5.9, 640^2: 4.15 against 3.23).
+int auto_depth(const sslbm_ctx *c) {
+    if (c->dtype == SSLBM_F32)
+        return 6;
+    return c->coef.diffuse_d ? 4 : 5;
+}
 int auto_cols(const sslbm_ctx *c) { return c->dtype == SSLBM_F32 ? 2 : 1; }
 
 // Rows per wavefront for which all wavefronts of the pass are resident at once
@@ -148,6 +154,28 @@ namespace sslbm {
 sslbm_status run_pass(sslbm_ctx *c, const void *in, void *out, int k, hipStream_t s) {
     return hip_status(c, launch_march(c->dtype, in, out, grid_of(c), c->coef, k,
                                       shape_for(c, k, in, out), s));
+}
+
+sslbm_status run_segment(sslbm_ctx *c, const void *src, void *dst, void *tmp0, void *tmp1,
+                         long long n, hipStream_t s) {
+    const TilePlan tiles = run_tiles(c, n);
+    const int K = tiles.rows ? tiles.depth : resolve(c).steps_per_pass;
+    const long long count = (n + K - 1) / K, longer = n % count;
+    const int base = (int)(n / count);
+    for (long long i = 0; i < count; ++i) {
+        const int k = i < longer ? base + 1 : base;
+        // the pass before the last one writes tmp0, so the last may read it
+        // and write dst = tmp1
+        void *out = i == count - 1 ? dst : ((count - 2 - i) % 2 == 0 ? tmp0 : tmp1);
+        const sslbm_status st =
+            tiles.rows ? hip_status(c, launch_tile(c->dtype, src, out, grid_of(c), c->coef, k,
+                                                   tiles.rows, s))
+                       : run_pass(c, src, out, k, s);
+        if (st != SSLBM_OK)
+            return st;
+        src = out;
+    }
+    return SSLBM_OK;
 }
 
 sslbm_status run_pass_mid2(sslbm_ctx *c, const void *in, void *mid, void *out, hipStream_t s) {
