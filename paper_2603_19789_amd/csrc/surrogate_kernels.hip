@@ -15,7 +15,8 @@
 // consecutive k values 8 (l / 16) .. 8 (l / 16) + 7, and receives rows
 // 4 (l / 16) + i, i = 0..3, of column l % 16 of the 16 x 16 FP32 result
 // (layout checked on the device).
-//   forward:  rows = output pixels, columns = output channels,
+//   forward:  rows = output pixels, columns = output channels (the other way
+//             round in the halo-tile kernel),
 //             k = (tap, input channel): both fragments are 16-byte loads of
 //             8 consecutive channels (NHWC activations, [out][tap][in] weights).
 //   backward data: the forward kernel on dZ with the weights flipped in
@@ -71,6 +72,66 @@ constexpr int BUF_FORMAT_WORD = 0x00020000;
 __device__ __forceinline__ u32x4 load16(__amdgpu_buffer_rsrc_t r, unsigned off) {
     return __builtin_bit_cast(
         u32x4, __builtin_bit_cast(unsigned __int128, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0)));
+}
+
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Two FP32 values rounded to BF16 (nearest even), the first in the low half.
+__device__ __forceinline__ unsigned pack_bf16x2(float a, float b) {
+    return __builtin_bit_cast(unsigned, bf16x2{(__bf16)a, (__bf16)b});
+}
+// Value i (0 or 1) of a pair, as FP32.
+__device__ __forceinline__ float half_bf16(unsigned pair, int i) {
+    return __builtin_bit_cast(float, i ? pair & 0xffff0000u : pair << 16);
+}
+// The value of the other lane of a pair (0, 1), (2, 3), ...
+__device__ __forceinline__ unsigned lane_pair_swap(unsigned v) {
+    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true);
+}
+
+// N channel pairs at a byte offset, of which those below `left` channels exist
+// (in eights where N holds more than four pairs: each 16 bytes are all in or
+// all out); the others read zeros or are dropped, as at an offset out of range.
+constexpr unsigned NO_ACCESS = 0x80000000u;
+template <int N>
+__device__ __forceinline__ void load_pairs(__amdgpu_buffer_rsrc_t r, unsigned off, int left,
+                                           unsigned (&v)[N]) {
+    static_assert(N == 1 || N == 2 || N % 4 == 0, "4, 8 or several 16-byte accesses");
+    if constexpr (N == 1) {
+        v[0] = __builtin_amdgcn_raw_buffer_load_b32(r, left > 0 ? off : NO_ACCESS, 0, 0);
+    } else if constexpr (N == 2) {
+        // split with shifts, as load16 and for the same reason
+        const unsigned long long w = __builtin_bit_cast(
+            unsigned long long,
+            __builtin_amdgcn_raw_buffer_load_b64(r, left > 0 ? off : NO_ACCESS, 0, 0));
+        v[0] = (unsigned)w;
+        v[1] = (unsigned)(w >> 32);
+    } else {
+#pragma unroll
+        for (int j = 0; j < N / 4; ++j) {
+            const u32x4 w = load16(r, left > 8 * j ? off + 16 * j : NO_ACCESS);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                v[4 * j + i] = w[i];
+        }
+    }
+}
+template <int N>
+__device__ __forceinline__ void store_pairs(__amdgpu_buffer_rsrc_t r, unsigned off, int left,
+                                            const unsigned (&v)[N]) {
+    if constexpr (N == 1) {
+        __builtin_amdgcn_raw_buffer_store_b32(v[0], r, left > 0 ? off : NO_ACCESS, 0, 0);
+    } else if constexpr (N == 2) {
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{v[0], v[1]}, r, left > 0 ? off : NO_ACCESS, 0,
+                                              0);
+    } else {
+#pragma unroll
+        for (int j = 0; j < N / 4; ++j)
+            __builtin_amdgcn_raw_buffer_store_b128(
+                u32x4{v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]}, r,
+                left > 8 * j ? off + 16 * j : NO_ACCESS, 0, 0);
+    }
 }
 
 __device__ __forceinline__ int wrap(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
@@ -294,8 +355,8 @@ constexpr int HALO_TH = 8, HALO_TW = 32;
 // LDS use (50 KB for 32 channels, 73 KB for 64) allows 3 or 2 workgroups
 // per CU; the register budget is held to the same occupancy. POOL: the
 // epilogue also writes the 2 x 2 means of the BF16 output (a wavefront's two
-// rows start at an even row and a lane's columns 4 g .. 4 g + 3 at an even
-// column, so every window lies in one lane), with the sums of the separate
+// rows start at an even row and lane pairs (m even, m + 1) at an even column,
+// so every window lies in one lane pair), with the sums of the separate
 // pooling kernel in its order, hence its bits.
 // UP: the first cu input channels are read from a half-resolution view
 // as its nearest 2x upsampling (pixel (y, x) reads (y / 2, x / 2)), so a
@@ -308,7 +369,7 @@ constexpr int HALO_TH = 8, HALO_TW = 32;
 // whose first a.cd input channels were a 2x upsampling): output channels
 // from a.cd on go to y, a view of a.cout - a.cd channels (channel c at
 // column c - a.cd); those below a.cd are kept in registers; each 2 x 2 window of
-// their BF16-rounded values (all in one lane, as for POOL) is summed in the
+// their BF16-rounded values (in one lane pair, as for POOL) is summed in the
 // order of the separate upsampling adjoint, rounded, passed through the
 // activation adjoint with a.du_mask when given, and written to the
 // half-resolution view a.du: the bits of the two separate passes.
@@ -357,9 +418,10 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
         a.bias ? a.cout * 4 : 0, BUF_FORMAT_WORD);
     const bool cload = tid < TC / 4;
 
-    // weight pieces: row (tap t, channel o of the group) of Bs, 8 channels k
-    // of the chunk; channels past the layer's load its last one (their
-    // results are never stored)
+    // weight pieces: row (tap t, position 16 ns + 4 q + i) of Bs, which holds
+    // output channel 4 NT q + 4 ns + i of the group, 8 channels k of the
+    // chunk; channels past the layer's load its last one (their results are
+    // never stored)
     unsigned boff[BPT], coff = 0;
     int bk[BPT], blds[BPT], bt[BPT], bo[BPT];
     bool bst[BPT];
@@ -369,7 +431,8 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
         bst[j] = e < BP;
         const int row = min(e >> 2, 9 * TC - 1), k = e & 3;
         bt[j] = row / TC;
-        bo[j] = row - bt[j] * TC;
+        const int pos = row - bt[j] * TC;  // 16 ns + 4 q + i
+        bo[j] = 4 * NT * (pos / 4 % 4) + 4 * (pos / 16) + pos % 4;
         bk[j] = 8 * k;
         blds[j] = row * LDA + 8 * k;
     }
@@ -493,13 +556,13 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
 #pragma unroll
                 for (int ns = 0; ns < NT; ++ns)
                     acc[ms][ns] =
-                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[ms], B[ns], acc[ms][ns], 0, 0, 0);
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[ns], A[ms], acc[ms][ns], 0, 0, 0);
         }
     };
-    // Output through a buffer descriptor: 32-bit offsets built from the
-    // row's offset (wavefront-uniform) and the lane's column and channel;
-    // pixels past the image's right edge and channels past the layer's get
-    // an offset past the range, and the hardware drops those stores.
+    // Output through a buffer descriptor: the row's offset is
+    // wavefront-uniform, the lane adds its column and channel; pixels past
+    // the image's right edge and channels past the layer's get an offset past
+    // the range, and the hardware drops those stores.
     constexpr int ESZ = F32OUT ? 4 : 2;
     // UPB: y holds only the channels from a.cd on (channel c at column c - cd)
     const int yc0 = UPB ? a.cd : 0;
@@ -524,129 +587,141 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
         umask ? const_cast<void *>(a.du_mask) : a.y, (short)0,
         umask ? (int)((((long long)a.n * hp * wp - 1) * a.du_mask_pitch + a.cd) * 2) : 0,
         BUF_FORMAT_WORD);
+    // The weights are the first operand of the matrix products and their rows
+    // are laid out so that a lane's NT tiles hold 4 NT consecutive channels
+    // (from 4 NT g) of pixel column m. It stores them, and reads masks, with
+    // 16-byte accesses, and the 64 lanes of one cover 16 whole pixels of the
+    // group's channels: 1 KB in a row where the view is as wide as the group.
+    // Views hold channels in eights (FP32: fours), so what one access covers
+    // is all in or all out. With pixels as the first operand instead, a lane
+    // held one channel of four pixels and stored 2 bytes at a time: the
+    // stores, and the mask loads, took longer than the products. 16 images of
+    // 256^2 pixels, batch passes before -> now: 32 channels 37 -> 32 us (134
+    // MB, 4.2 TB/s), pooled 41 -> 35, through a mask 58 -> 42; 64 channels of
+    // 128^2 pixels 27 -> 25, pooled 34 -> 29, through a mask 44 -> 32; the
+    // decoders' backward data 83 -> 71.
+    constexpr int PAIRS = 2 * NT;  // channel pairs of a lane
     auto epilogue = [&](int unit) {
         int n, y0, x0, cg;
         unit_origin(unit, n, y0, x0, cg);
         const int yr = y0 + 2 * wv;  // the wavefront's first row (even)
+        const int c0 = cg * TC + 4 * NT * g;
+        // UPB: the lane's channels belong to the upsampled input (cd is a
+        // multiple of 16, so all of them or none)
+        const bool up_block = UPB && c0 < a.cd;
+        bool x_ok[2];
+        unsigned yoff[2], moff[2];
 #pragma unroll
-        for (int ns = 0; ns < NT; ++ns) {
-            const int c = cg * TC + 16 * ns + m;
-            const bool c_ok = c < a.cout;
-            const float b = Cs[16 * ns + m];
-            // UPB: this 16-channel block belongs to the upsampled input
-            // (wavefront-uniform; cd is a multiple of 16)
-            const bool up_block = UPB && cg * TC + 16 * ns < a.cd;
-            float fv[4][4];  // the stored BF16 values, as floats (POOL, UPB)
+        for (int half = 0; half < 2; ++half) {
+            const int x = x0 + 16 * half + m;
+            x_ok[half] = x < a.w;
+            yoff[half] = (unsigned)x * ypb + (unsigned)((c0 - yc0) * ESZ);
+            moff[half] = (unsigned)x * mpb + (unsigned)(c0 * 2);
+        }
+        unsigned hv[4][PAIRS];  // the stored BF16 values, channel pairs (not FP32)
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                if (yr + r >= a.h)
-                    continue;  // wavefront-uniform
-                // the activation's outputs at the row's 8 values of this lane
-                // (MASK only), all requested before the first is used
-                unsigned short mk[4][4];
-                if constexpr (MASK) {
-                    const unsigned mrow =
-                        (unsigned)((((long long)n * a.h + yr + r) * a.w + x0) * mpb) +
-                        (unsigned)(4 * g) * mpb + (unsigned)(c * 2);
+        for (int r = 0; r < 2; ++r) {
+            if (yr + r >= a.h)
+                continue;  // wavefront-uniform
+            const long long row = ((long long)n * a.h + yr + r) * a.w;
+            const unsigned yrow = (unsigned)(row * ypb), mrow = (unsigned)(row * mpb);
+            // the activation's outputs at the row's values of this lane
+            // (MASK only), all requested before the first is used
+            unsigned mk[2][PAIRS];
+            if constexpr (MASK) {
 #pragma unroll
-                    for (int ms = 2 * r; ms < 2 * r + 2; ++ms)
+                for (int half = 0; half < 2; ++half)
+                    load_pairs<PAIRS>(mr, x_ok[half] ? mrow + moff[half] : OUT_OF_RANGE,
+                                      a.cout - c0, mk[half]);
+            }
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const int col = 16 * (ms % 2) + i;
-                            const bool ok = c_ok && x0 + col + 4 * g < a.w;
-                            mk[ms][i] = __builtin_amdgcn_raw_buffer_load_b16(
-                                mr, ok ? mrow + (unsigned)col * mpb : OUT_OF_RANGE, 0, 0);
-                        }
-                }
-                const unsigned lane_off =
-                    (unsigned)((((long long)n * a.h + yr + r) * a.w + x0) * ypb) +
-                    (unsigned)(4 * g) * ypb + (unsigned)((c - yc0) * ESZ);
+            for (int half = 0; half < 2; ++half) {
+                const int ms = 2 * r + half;
+                const unsigned off = x_ok[half] ? yrow + yoff[half] : OUT_OF_RANGE;
 #pragma unroll
-                for (int ms = 2 * r; ms < 2 * r + 2; ++ms)
+                for (int ns = 0; ns < NT; ++ns) {
+                    const f32x4 b = *reinterpret_cast<const f32x4 *>(&Cs[4 * NT * g + 4 * ns]);
+                    f32x4 v;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int col = 16 * (ms % 2) + i;  // plus 4 g
-                        const bool ok = c_ok && x0 + col + 4 * g < a.w;
-                        const unsigned off = ok ? lane_off + (unsigned)col * ypb : OUT_OF_RANGE;
-                        float v = acc[ms][ns][i] + b;
+                        v[i] = acc[ms][ns][i] + b[i];
                         if (LEAKY)
-                            v = v > 0.f ? v : a.slope * v;
-                        if (F32OUT) {
-                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v),
-                                                                  yr_, off, 0, 0);
-                        } else {
-                            unsigned short hv = __builtin_bit_cast(unsigned short, (__bf16)v);
-                            if constexpr (MASK) {
-                                const float d = __builtin_bit_cast(float, (unsigned)hv << 16);
-                                const float mv =
-                                    __builtin_bit_cast(float, (unsigned)mk[ms][i] << 16);
-                                hv = to_bf16(mv > 0.f ? d : a.slope * d);
+                            v[i] = v[i] > 0.f ? v[i] : a.slope * v[i];
+                    }
+                    if constexpr (F32OUT) {
+                        __builtin_amdgcn_raw_buffer_store_b128(
+                            __builtin_bit_cast(u32x4, v), yr_,
+                            c0 + 4 * ns < a.cout ? off + (unsigned)(16 * ns) : OUT_OF_RANGE, 0, 0);
+                    } else {
+                        hv[ms][2 * ns] = pack_bf16x2(v[0], v[1]);
+                        hv[ms][2 * ns + 1] = pack_bf16x2(v[2], v[3]);
+                    }
+                }
+                if constexpr (!F32OUT) {
+                    if constexpr (MASK) {
+#pragma unroll
+                        for (int q = 0; q < PAIRS; ++q) {
+                            float d[2];
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) {
+                                d[i] = half_bf16(hv[ms][q], i);
+                                d[i] = half_bf16(mk[half][q], i) > 0.f ? d[i] : a.slope * d[i];
                             }
-                            if (!up_block)
-                                __builtin_amdgcn_raw_buffer_store_b16(hv, yr_, off, 0, 0);
-                            if (POOL || UPB)
-                                fv[ms][i] = __builtin_bit_cast(float, (unsigned)hv << 16);
+                            hv[ms][q] = pack_bf16x2(d[0], d[1]);
                         }
                     }
-            }
-            if constexpr (UPB) {
-                if (up_block && yr + 1 < a.h) {  // wavefront-uniform; h is even
-                    const long long lrow = ((long long)n * hp + yr / 2) * wp;
-                    const unsigned urow = (unsigned)((lrow * a.du_pitch + c) * 2);
-                    const unsigned mrow = (unsigned)((lrow * a.du_mask_pitch + c) * 2);
-                    // window (rows yr, yr + 1; columns x, x + 1), x = x0 + 16 ms + 4 g + i
-                    unsigned off[2][2];
-                    unsigned short um[2][2];
-#pragma unroll
-                    for (int ms = 0; ms < 2; ++ms)
-#pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            const int x = x0 + 16 * ms + 4 * g + 2 * j;
-                            const bool ok = c_ok && x < a.w;
-                            off[ms][j] = ok ? urow + (unsigned)(x / 2 * a.du_pitch * 2)
-                                            : OUT_OF_RANGE;
-                            if (umask)
-                                um[ms][j] = __builtin_amdgcn_raw_buffer_load_b16(
-                                    umr, ok ? mrow + (unsigned)(x / 2 * a.du_mask_pitch * 2)
-                                            : OUT_OF_RANGE,
-                                    0, 0);
-                        }
-#pragma unroll
-                    for (int ms = 0; ms < 2; ++ms)
-#pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            const int i = 2 * j;
-                            const float sum =
-                                ((fv[ms][i] + fv[ms][i + 1]) + fv[ms + 2][i]) + fv[ms + 2][i + 1];
-                            unsigned short hs = to_bf16(sum);
-                            if (umask) {
-                                const float d = __builtin_bit_cast(float, (unsigned)hs << 16);
-                                const float mv = __builtin_bit_cast(float, (unsigned)um[ms][j] << 16);
-                                hs = to_bf16(mv > 0.f ? d : a.slope * d);
-                            }
-                            __builtin_amdgcn_raw_buffer_store_b16(hs, ur, off[ms][j], 0, 0);
-                        }
+                    if (!up_block)
+                        store_pairs<PAIRS>(yr_, off, a.cout - c0, hv[ms]);
                 }
             }
-            if constexpr (POOL && !F32OUT) {
-                if (yr + 1 < a.h) {  // wavefront-uniform; h is even
-                    const unsigned prow =
-                        (unsigned)(((((long long)n * hp + yr / 2) * wp) * a.pool_pitch + c) * 2);
-                    // window (rows yr, yr + 1; columns x, x + 1), x = x0 + 16 ms + 4 g + i
+        }
+        if constexpr ((POOL || UPB) && !F32OUT) {
+            // 2 x 2 windows: rows yr, yr + 1; columns of the lane pair (m even,
+            // m + 1). The even lane takes the first half of the channels and
+            // the odd one the second, so each sends the other half.
+            if ((POOL || up_block) && yr + 1 < a.h) {  // h is even
+                const long long lrow = ((long long)n * hp + yr / 2) * wp;
+                const bool odd = m & 1;
+                const int c = c0 + (odd ? 2 * NT : 0);
 #pragma unroll
-                    for (int ms = 0; ms < 2; ++ms)
+                for (int half = 0; half < 2; ++half) {
+                    const long long pix = lrow + (x0 + 16 * half + m) / 2;
+                    unsigned um[NT], out[NT];
+                    if (UPB && umask)
+                        load_pairs<NT>(umr,
+                                       x_ok[half] ? (unsigned)((pix * a.du_mask_pitch + c) * 2)
+                                                  : OUT_OF_RANGE,
+                                       a.cd - c, um);
 #pragma unroll
-                        for (int i = 0; i < 4; i += 2) {
-                            const int x = x0 + 16 * ms + 4 * g + i;
-                            const float sum =
-                                ((fv[ms][i] + fv[ms][i + 1]) + fv[ms + 2][i]) + fv[ms + 2][i + 1];
-                            const unsigned off =
-                                c_ok && x < a.w ? prow + (unsigned)(x / 2 * a.pool_pitch * 2)
-                                                : OUT_OF_RANGE;
-                            __builtin_amdgcn_raw_buffer_store_b16(
-                                __builtin_bit_cast(unsigned short, (__bf16)(0.25f * sum)), pr, off,
-                                0, 0);
+                    for (int q = 0; q < NT; ++q) {
+                        unsigned win[2][2];  // [row][column]
+#pragma unroll
+                        for (int r = 0; r < 2; ++r) {
+                            const unsigned first = hv[2 * r + half][q];
+                            const unsigned second = hv[2 * r + half][NT + q];
+                            const unsigned keep = odd ? second : first;
+                            const unsigned got = lane_pair_swap(odd ? first : second);
+                            win[r][0] = odd ? got : keep;
+                            win[r][1] = odd ? keep : got;
                         }
+                        float o[2];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            const float sum = ((half_bf16(win[0][0], i) + half_bf16(win[0][1], i)) +
+                                               half_bf16(win[1][0], i)) +
+                                              half_bf16(win[1][1], i);
+                            o[i] = POOL ? 0.25f * sum : sum;
+                            if (UPB && umask) {
+                                const float d = half_bf16(pack_bf16x2(sum, sum), 0);
+                                o[i] = half_bf16(um[q], i) > 0.f ? d : a.slope * d;
+                            }
+                        }
+                        out[q] = pack_bf16x2(o[0], o[1]);
+                    }
+                    const unsigned pitch = (unsigned)(POOL ? a.pool_pitch : a.du_pitch);
+                    store_pairs<NT>(POOL ? pr : ur,
+                                    x_ok[half] ? (unsigned)((pix * pitch + c) * 2) : OUT_OF_RANGE,
+                                    (POOL ? a.cout : a.cd) - c, out);
                 }
             }
         }
