@@ -352,8 +352,22 @@ __global__ __launch_bounds__(THREADS) void conv_fwd_kernel(ConvArgs a) {
 // (a halo wraps at most once).
 constexpr int HALO_TH = 8, HALO_TW = 32;
 
-// LDS use (50 KB for 32 channels, 73 KB for 64) allows 3 or 2 workgroups
-// per CU; the register budget is held to the same occupancy. POOL: the
+// LDS rows of 32 channels (64 bytes, a quarter of the 64 banks) without
+// padding: the 16-byte piece k of row or column i is held at piece
+// k ^ lds_turn(i), so that 16 consecutive rows read at one piece fall on all
+// banks. Measured over the 256 CUs, 16-byte reads of 16 rows: 232 bytes per
+// CU and clock so, 121 with rows padded to 80 bytes; transpose loads (8
+// bytes): 194 and 109.
+__device__ __forceinline__ constexpr int lds_turn(int i) { return i >> 1 & 3; }
+
+// 3 workgroups per CU for up to 32 channels (40 KB of LDS, 160 registers), 2
+// for 64 (59 KB, 240 registers): the register budget is held to that. What
+// bounds it now (16 images): plain 32-channel layers of 256^2 pixels the
+// memory (31 us for 134 MB, 4.3 TB/s), 192 -> 64 channels of 128^2 pixels the
+// products (56 us, 1.04 PFLOP/s; without the loads 44, without the products
+// 35). With padded LDS rows, where every read took twice the cycles, and
+// fragments read right before their use, that layer took 61 us, 96 -> 32
+// channels of 256^2 pixels 83 (now 78). POOL: the
 // epilogue also writes the 2 x 2 means of the BF16 output (a wavefront's two
 // rows start at an even row and lane pairs (m even, m + 1) at an even column,
 // so every window lies in one lane pair), with the sums of the separate
@@ -384,9 +398,9 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
     constexpr int TC = 16 * NT;
     constexpr int BP = 9 * TC * 4, BPT = (BP + THREADS - 1) / THREADS;
     constexpr unsigned OUT_OF_RANGE = 0x80000000u;
-    __shared__ __attribute__((aligned(16))) uint16_t Hs[HPIX * LDA];
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[9 * TC * LDA];
-    __shared__ __attribute__((aligned(16))) float Cs[TC];  // bias of the group
+    __shared__ __attribute__((aligned(16))) uint16_t Hs[HPIX * 32];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[9 * TC * 32];
+    __shared__ __attribute__((aligned(16))) float Cs[2][TC];  // bias of two items' groups
 
     const int G = gridDim.x;
     if ((int)blockIdx.x >= units)
@@ -419,33 +433,29 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
     const bool cload = tid < TC / 4;
 
     // weight pieces: row (tap t, position 16 ns + 4 q + i) of Bs, which holds
-    // output channel 4 NT q + 4 ns + i of the group, 8 channels k of the
+    // output channel 4 NT q + 4 ns + i of the group, 8 channels hk of the
     // chunk; channels past the layer's load its last one (their results are
-    // never stored)
-    unsigned boff[BPT], coff = 0;
-    int bk[BPT], blds[BPT], bt[BPT], bo[BPT];
-    bool bst[BPT];
-#pragma unroll
-    for (int j = 0; j < BPT; ++j) {
-        const int e = tid + THREADS * j;
-        bst[j] = e < BP;
-        const int row = min(e >> 2, 9 * TC - 1), k = e & 3;
-        bt[j] = row / TC;
-        const int pos = row - bt[j] * TC;  // 16 ns + 4 q + i
-        bo[j] = 4 * NT * (pos / 4 % 4) + 4 * (pos / 16) + pos % 4;
-        bk[j] = 8 * k;
-        blds[j] = row * LDA + 8 * k;
-    }
+    // never stored). Piece j of a thread is row (tid >> 2) + 64 j: the same
+    // position for every j, 64 / TC taps apart.
+    const int hk = 8 * (tid & 3);
+    const int bpos = (tid >> 2) % TC, btap = (tid >> 2) / TC;
+    const int bo = 4 * NT * (bpos / 4 % 4) + 4 * (bpos / 16) + bpos % 4;
+    const int blds = (tid >> 2) * 32 + (hk ^ 8 * lds_turn(bpos));
+    auto bst = [&](int j) { return btap + 64 / TC * j < 9; };
+    const unsigned bstep = (unsigned)(64 / TC * a.cin * 2);
+    unsigned boff = 0, coff = 0;
     // halo pieces: pixel hp of the halo tile, 8 channels k of the chunk
     // (hoffu: the same pixel in the half-resolution view)
     // (piece j of a thread: pixel (tid >> 2) + 64 j, the same 8 channels
-    // hk for every j, LDS slot hlds + 64 j LDA; the pixel's row and column
-    // are recomputed where needed rather than kept in registers)
+    // hk for every j; the pixel's row and column are recomputed where needed
+    // rather than kept in registers)
     unsigned hoff[HPT], hoffu[HPT];
-    const int hk = 8 * (tid & 3);
-    const int hlds = (tid >> 2) * LDA + hk;
+    unsigned hturn = 0;  // the turns of the HPT pixels, two bits each
     auto hpix = [&](int j) { return min((tid >> 2) + 64 * j, HPIX - 1); };
     auto hst = [&](int j) { return tid + THREADS * j < HP; };
+#pragma unroll
+    for (int j = 0; j < HPT; ++j)
+        hturn |= (unsigned)lds_turn(hpix(j) % HW2) << (2 * j);
     auto unit_origin = [&](int unit, int &n, int &y0, int &x0, int &cg) {
         const int tile = unit / groups;
         cg = unit - tile * groups;
@@ -468,11 +478,8 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
                 hoffu[j] = (unsigned)(
                     ((((long long)n * hu + (y >> 1)) * wu + (x >> 1)) * a.xu_pitch + hk) * 2);
         }
-#pragma unroll
-        for (int j = 0; j < BPT; ++j) {
-            const int o = min(cg * TC + bo[j], a.cout - 1);
-            boff[j] = (unsigned)(((o * 9 + bt[j]) * a.cin + bk[j]) * 2);
-        }
+        const int o = min(cg * TC + bo, a.cout - 1);
+        boff = (unsigned)(((o * 9 + btap) * a.cin + hk) * 2);
         coff = cload ? (unsigned)((cg * TC + 4 * tid) * 4) : OUT_OF_RANGE;
     };
 
@@ -505,23 +512,25 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
         if (weights) {
 #pragma unroll
             for (int j = 0; j < BPT; ++j)
-                r.b[j] = load16(wr, bst[j] && bk[j] < left ? boff[j] + c2 : OUT_OF_RANGE);
+                r.b[j] = load16(wr, bst(j) && hk < left ? boff + (c2 + j * bstep) : OUT_OF_RANGE);
             r.c = load16(br, coff);
         }
         return r;
     };
-    auto lstore = [&](const Stage &r, bool weights) {
+    auto lstore = [&](const Stage &r, bool weights, int slot) {
 #pragma unroll
         for (int j = 0; j < HPT; ++j)
             if (hst(j))
-                *reinterpret_cast<u32x4 *>(&Hs[hlds + 64 * j * LDA]) = r.h[j];
+                *reinterpret_cast<u32x4 *>(
+                    &Hs[((tid >> 2) + 64 * j) * 32 +
+                        (hk ^ (int)(8 * (hturn >> (2 * j) & 3)))]) = r.h[j];
         if (weights) {
 #pragma unroll
             for (int j = 0; j < BPT; ++j)
-                if (bst[j])
-                    *reinterpret_cast<u32x4 *>(&Bs[blds[j]]) = r.b[j];
+                if (bst(j))
+                    *reinterpret_cast<u32x4 *>(&Bs[blds + 64 * j * 32]) = r.b[j];
             if (cload)
-                *reinterpret_cast<u32x4 *>(&Cs[4 * tid]) = r.c;
+                *reinterpret_cast<u32x4 *>(&Cs[slot][4 * tid]) = r.c;
         }
     };
     f32x4 acc[4][NT];
@@ -535,29 +544,58 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
     // fragment ms of wavefront wv: tile row 2 wv + ms / 2, columns
     // 16 (ms % 2) .. + 15; at tap (dy, dx) it reads halo pixel
     // (row + 1 + dy, column + 1 + dx)
-    const uint16_t *ha = &Hs[(2 * wv * HW2 + m) * LDA + 8 * g];
-    const uint16_t *hb = &Bs[m * LDA + 8 * g];
+    const uint16_t *ha[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+        ha[dx] = &Hs[(2 * wv * HW2 + m + dx) * 32 + 8 * (g ^ lds_turn(m + dx))];
+    const uint16_t *hb = &Bs[m * 32 + 8 * (g ^ lds_turn(m))];
+    // A tap's fragments are read while the tap before is multiplied: the
+    // group barriers below hold the schedule to one LDS read per MFMA or two.
+    // Left to itself the compiler reads each fragment right before its use
+    // and waits for LDS three times a tap.
     auto taps = [&]() {
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
+        bf16x8 A[2][4], B[2][NT];
+        auto fragments = [&](int t) {
             const int dy = t / 3, dx = t % 3;  // shifted by one
-            bf16x8 A[4], B[NT];
-#pragma unroll
-            for (int ms = 0; ms < 4; ++ms)
-                A[ms] = __builtin_bit_cast(
-                    bf16x8, *reinterpret_cast<const uint4 *>(
-                                ha + ((ms / 2 + dy) * HW2 + 16 * (ms % 2) + dx) * LDA));
 #pragma unroll
             for (int ns = 0; ns < NT; ++ns)
-                B[ns] = __builtin_bit_cast(
-                    bf16x8, *reinterpret_cast<const uint4 *>(hb + (t * TC + 16 * ns) * LDA));
+                B[t % 2][ns] = __builtin_bit_cast(
+                    bf16x8, *reinterpret_cast<const uint4 *>(hb + (t * TC + 16 * ns) * 32));
+#pragma unroll
+            for (int ms = 0; ms < 4; ++ms)
+                A[t % 2][ms] = __builtin_bit_cast(
+                    bf16x8, *reinterpret_cast<const uint4 *>(
+                                ha[dx] + ((ms / 2 + dy) * HW2 + 16 * (ms % 2)) * 32));
+        };
+        fragments(0);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            if (t < 8)
+                fragments(t + 1);
 #pragma unroll
             for (int ms = 0; ms < 4; ++ms)
 #pragma unroll
                 for (int ns = 0; ns < NT; ++ns)
-                    acc[ms][ns] =
-                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[ns], A[ms], acc[ms][ns], 0, 0, 0);
+                    acc[ms][ns] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        B[t % 2][ns], A[t % 2][ms], acc[ms][ns], 0, 0, 0);
         }
+        if constexpr (NT < 4)
+            return;  // three wavefronts per SIMD hide it; a second set of fragments spills
+        constexpr int READS = 4 + NT, PRODUCTS = 4 * NT, EACH = PRODUCTS / READS ? PRODUCTS / READS : 1;
+        constexpr int MFMA = 0x8, LDS_READ = 0x100;
+        __builtin_amdgcn_sched_group_barrier(LDS_READ, READS, 0);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+#pragma unroll
+            for (int i = 0; i < READS; ++i) {
+                __builtin_amdgcn_sched_group_barrier(LDS_READ, 1, 0);
+                if ((i + 1) * EACH <= PRODUCTS)
+                    __builtin_amdgcn_sched_group_barrier(MFMA, EACH, 0);
+            }
+            if (PRODUCTS > READS * EACH)
+                __builtin_amdgcn_sched_group_barrier(MFMA, PRODUCTS - READS * EACH, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(MFMA, PRODUCTS, 0);
     };
     // Output through a buffer descriptor: the row's offset is
     // wavefront-uniform, the lane adds its column and channel; pixels past
@@ -601,7 +639,7 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
     // 128^2 pixels 27 -> 25, pooled 34 -> 29, through a mask 44 -> 32; the
     // decoders' backward data 83 -> 71.
     constexpr int PAIRS = 2 * NT;  // channel pairs of a lane
-    auto epilogue = [&](int unit) {
+    auto epilogue = [&](int unit, const float *bias) {
         int n, y0, x0, cg;
         unit_origin(unit, n, y0, x0, cg);
         const int yr = y0 + 2 * wv;  // the wavefront's first row (even)
@@ -640,7 +678,7 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
                 const unsigned off = x_ok[half] ? yrow + yoff[half] : OUT_OF_RANGE;
 #pragma unroll
                 for (int ns = 0; ns < NT; ++ns) {
-                    const f32x4 b = *reinterpret_cast<const f32x4 *>(&Cs[4 * NT * g + 4 * ns]);
+                    const f32x4 b = *reinterpret_cast<const f32x4 *>(&bias[4 * NT * g + 4 * ns]);
                     f32x4 v;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -729,8 +767,7 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
 
     int unit = vb, chunk = 0;
     unit_offsets(unit);
-    Stage st = gload(0, true);
-    lstore(st, true);
+    lstore(gload(0, true), true, 0);
     __syncthreads();
     clear();
     // with one chunk and one channel group the weights stay in LDS
@@ -742,19 +779,24 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
             nunit += G;
         }
         const bool more = it + 1 < items;
+        Stage next;
         if (more) {
             if (nunit != unit)
                 unit_offsets(nunit);
-            st = gload(nchunk, reload_b);
+            next = gload(nchunk, reload_b);
         }
         taps();
+        __syncthreads();  // every wavefront is done with the LDS tiles
+        // The next tiles go to LDS before the results are stored: a wait for
+        // loads also waits for the stores issued after them (32
+        // channels with means, 16 images of 256^2 pixels: 36 to 41 us with the
+        // stores first, 34 so).
+        if (more)
+            lstore(next, reload_b, (it + 1) & 1);
         if (chunk == nck - 1) {
-            epilogue(unit);
+            epilogue(unit, Cs[reload_b ? it & 1 : 0]);
             clear();
         }
-        __syncthreads();  // every wavefront is done with the LDS tiles
-        if (more)
-            lstore(st, reload_b);
         __syncthreads();
         unit = nunit;
         chunk = nchunk;
@@ -1027,8 +1069,8 @@ __global__ __launch_bounds__(THREADS) void conv_wgrad_kernel(WgradArgs a) {
 constexpr int WH_TH = 8, WH_TW = 32;     // pixel tile
 constexpr int WH_HW = WH_TW + 2;         // halo tile columns
 constexpr int WH_HPIX = (WH_TH + 2) * WH_HW;
-constexpr int WH_PZ = 40;  // LDS row pitch (elements) of a dZ pixel: 16-byte stores
-constexpr int WH_PX = 40;  // and of an input pixel
+constexpr int WH_PZ = 32;  // LDS row pitch (elements) of a dZ pixel, pieces turned by lds_turn
+constexpr int WH_PX = 32;  // and of an input pixel (of the column, both)
 constexpr int WH_ZP = WH_TH * WH_TW * 4 / THREADS;           // 16-byte pieces a thread loads
 constexpr int WH_XP = (WH_HPIX * 4 + THREADS - 1) / THREADS;
 constexpr int WH_RESIDENT = 512;         // two workgroups per CU on 256 CUs
@@ -1131,14 +1173,22 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
         }
         return st;
     };
+    // dZ pixel columns repeat every 32 pixels: one turn for all pieces
+    const int jz = j8 ^ 8 * lds_turn(tid >> 2 & (WH_TW - 1));
+    unsigned xturn = 0;  // the turns of the WH_XP input pixels, two bits each
+#pragma unroll
+    for (int r = 0; r < WH_XP; ++r)
+        xturn |= (unsigned)lds_turn(((tid >> 2) + 64 * r) % WH_HW) << (2 * r);
     auto lstore = [&](const Stage &st) {
 #pragma unroll
         for (int r = 0; r < WH_ZP; ++r)
-            *reinterpret_cast<u32x4 *>(&Zs[((tid >> 2) + 64 * r) * WH_PZ + j8]) = st.z[r];
+            *reinterpret_cast<u32x4 *>(&Zs[((tid >> 2) + 64 * r) * WH_PZ + jz]) = st.z[r];
 #pragma unroll
         for (int r = 0; r < WH_XP; ++r)
             if ((tid >> 2) + 64 * r < WH_HPIX)
-                *reinterpret_cast<u32x4 *>(&Xs[((tid >> 2) + 64 * r) * WH_PX + j8]) = st.x[r];
+                *reinterpret_cast<u32x4 *>(
+                    &Xs[((tid >> 2) + 64 * r) * WH_PX + (j8 ^ (int)(8 * (xturn >> (2 * r) & 3)))]) =
+                    st.x[r];
     };
 
     f32x4 acc[9][2][2];
@@ -1154,9 +1204,17 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
 
     // this lane's transpose-load addresses (elements): pixel row offset q
     // within a group of four, channel offset 4 r
+    // (elements from the tile's start: in piece tc / 8 of 16-channel half 0,
+    // element tc % 8; the half is bit 1 of the piece, and so is what the turn
+    // of a pixel four further on differs by)
     const int tq = 8 * g + (m >> 2), tc = 4 * (m & 3);
-    const uint16_t *za = Zs + (2 * wv * WH_TW + tq) * WH_PZ + tc;
-    const uint16_t *xa = Xs + (2 * wv * WH_HW + tq) * WH_PX + tc;
+    auto turned = [&](int col) { return ((tc >> 3) ^ lds_turn(col)) * 8 + (tc & 7); };
+    const int za = (2 * wv * WH_TW + tq) * WH_PZ + turned(tq);
+    const int xa0 = (2 * wv * WH_HW + tq) * WH_PX;
+    int xa[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+        xa[dx] = xa0 + dx * WH_PX + turned(tq + dx);
 
     int tile = kb;
     if (tile < a.tiles)
@@ -1171,7 +1229,7 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const u32x4 v = *reinterpret_cast<const u32x4 *>(
-                    &Zs[((tid >> 2) + 64 * r) * WH_PZ + j8]);
+                    &Zs[((tid >> 2) + 64 * r) * WH_PZ + jz]);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     bsum[2 * k] += __builtin_bit_cast(float, v[k] << 16);
@@ -1185,19 +1243,23 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const uint16_t *p = za + (kk * WH_TW) * WH_PZ + 16 * u;
-                A[kk][u] = tr_fragment(p, p + 4 * WH_PZ);
+                // (bit 1 of tq's turn is clear: the halves are 16 apart)
+                const uint16_t *p = Zs + za + kk * WH_TW * WH_PZ;
+                A[kk][u] = tr_fragment(p + 16 * u, p + 4 * WH_PZ + 16 * (1 - u));
             }
 #pragma unroll
-        for (int dx = 0; dx < 3; ++dx)
+        for (int dx = 0; dx < 3; ++dx) {
+            // the other half, kept out of the loop-invariant registers
+            asm volatile("" : "+v"(xa[dx]));
+            const int half[2] = {xa[dx], xa[dx] ^ 16};
 #pragma unroll
             for (int v = 0; v < 2; ++v) {
                 // halo rows 2 wv + rr, rr = kk + dy
                 bf16x8 B[4];
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr) {
-                    const uint16_t *p = xa + (rr * WH_HW + dx) * WH_PX + 16 * v;
-                    B[rr] = tr_fragment(p, p + 4 * WH_PX);
+                    B[rr] = tr_fragment(Xs + half[v] + rr * WH_HW * WH_PX,
+                                        Xs + half[1 - v] + (rr * WH_HW + 4) * WH_PX);
                 }
 #pragma unroll
                 for (int dy = 0; dy < 3; ++dy)
@@ -1208,6 +1270,7 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
                             acc[3 * dy + dx][u][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                                 A[kk][u], B[kk + dy], acc[3 * dy + dx][u][v], 0, 0, 0);
             }
+        }
         __syncthreads();  // every wavefront is done with the tiles
         if (more)
             lstore(next);
@@ -1529,20 +1592,28 @@ __global__ __launch_bounds__(THREADS) void pack_input_kernel(const float *__rest
 }
 
 // rho_next[b, c] = rho[b, c] + scale_out_c * out[b, y, x, c] for c < 5
-__global__ __launch_bounds__(THREADS) void apply_output_kernel(const float *__restrict__ rho,
+// One thread per pixel: its five channels lie in one 64-byte line of out,
+// which a thread per value read five times over, 64 lines per access (16
+// images of 256^2 pixels: 30 us before, 17 us now for 109 MB).
+__global__ __launch_bounds__(THREADS) void apply_output_kernel(const float *rho,
                                                                const float *__restrict__ out,
                                                                int batch, int h, int w,
-                                                               IoScales s,
-                                                               float *__restrict__ next) {
-    const long long e = (long long)blockIdx.x * THREADS + threadIdx.x;
+                                                               IoScales s, float *next) {
+    const long long q = (long long)blockIdx.x * THREADS + threadIdx.x;
     const long long hw = (long long)h * w;
-    if (e >= batch * hw * 5)
+    if (q >= batch * hw)
         return;
-    const long long p = e % hw;
-    const long long bc = e / hw;
-    const int c = (int)(bc % 5);
-    const long long b = bc / 5;
-    next[e] = rho[e] + s.out[c] * out[(b * hw + p) * SUR_OUT_CHANNELS + c];
+    const long long b = q / hw, p = q - b * hw;
+    const float *o = out + q * SUR_OUT_CHANNELS;
+    float v[5], r[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+        v[c] = o[c];
+        r[c] = rho[(b * 5 + c) * hw + p];
+    }
+#pragma unroll
+    for (int c = 0; c < 5; ++c)
+        next[(b * 5 + c) * hw + p] = r[c] + s.out[c] * v[c];
 }
 
 // Loss = mean over (b, y, x, c < 5) of (out - (target - rho) / scale_out)^2;
@@ -2026,7 +2097,7 @@ hipError_t launch_pack_input(const float *rho, int batch, int h, int w, const fl
 
 hipError_t launch_apply_output(const float *rho, const float *out, int batch, int h, int w,
                                const IoScales &sc, float *next, hipStream_t s) {
-    hipLaunchKernelGGL(apply_output_kernel, dim3(blocks_for((long long)batch * h * w * 5)),
+    hipLaunchKernelGGL(apply_output_kernel, dim3(blocks_for((long long)batch * h * w)),
                        dim3(THREADS), 0, s, rho, out, batch, h, w, sc, next);
     return hipGetLastError();
 }
