@@ -1059,10 +1059,16 @@ __global__ __launch_bounds__(THREADS) void conv_wgrad_kernel(WgradArgs a) {
 // the pixel rows, so one copy of the input tile serves all nine taps.
 // Wavefront w takes tile rows 2w and 2w + 1 as its k steps (32 pixels
 // each). For each horizontal shift it reads the four halo rows those steps
-// touch once and uses each for every vertical shift it serves (12 MFMAs per
-// pair of fragments); the next tile's loads are in flight meanwhile. The four
-// wavefronts' sums are added in LDS and written as the workgroup's split of
-// the fixed-order reduction below. The workgroups of input block 0 also sum
+// touch once, two fragments ahead of their use, and uses each for every
+// vertical shift it serves (2 or 4 MFMAs per fragment); the next tile's loads
+// are in flight meanwhile. The four wavefronts' sums are added in LDS, by all
+// threads, and written as the workgroup's split of the fixed-order reduction
+// below. The registers bound it: 144 of 256 hold sums, so there are 2
+// wavefronts per SIMD and what one waits for shows. 16 images of 256^2
+// pixels, 32 -> 32 channels: 41 us with fragments read right before their use
+// and the wavefronts' sums added one wavefront at a time, 36 now (134 MB: 26
+// us at the rate of a copy); 192 -> 64 channels of 128^2 pixels 88 us, now 83
+// (58 GFLOP: 47 us at the rate of a large matrix product). The workgroups of input block 0 also sum
 // the dZ tile per output channel (the bias gradient): thread (pixel group
 // s, channels 8 j .. 8 j + 7) over pixels s, s + 64, s + 128, s + 192 of
 // every tile; the 64 sums of a channel are then added in order.
@@ -1108,6 +1114,9 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t lds[WH_LDS];
     uint16_t *const Zs = lds;
     uint16_t *const Xs = lds + WH_TH * WH_TW * WH_PZ;
+    // bias sums of channels 8 (tid % 4) .. + 7, a thread's own (in registers
+    // they would spill)
+    __shared__ f32x4 bsum[2][THREADS];
     constexpr unsigned OUT_OF_RANGE = 0x80000000u;
     const int blocks = a.nob * a.nib;
     // Workgroup b runs on XCD b % 8, each with its own L2: the channel
@@ -1200,7 +1209,7 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
             for (int v = 0; v < 2; ++v)
                 acc[t][u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
     const bool bias_block = ib == 0;
-    float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // channels 8 (tid % 4) ..
+    bsum[0][tid] = bsum[1][tid] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // this lane's transpose-load addresses (elements): pixel row offset q
     // within a group of four, channel offset 4 r
@@ -1226,17 +1235,28 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
         if (more)
             next = gload(tile + a.gb);
         if (bias_block) {
+            f32x4 lo = bsum[0][tid], hi = bsum[1][tid];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const u32x4 v = *reinterpret_cast<const u32x4 *>(
                     &Zs[((tid >> 2) + 64 * r) * WH_PZ + jz]);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    bsum[2 * k] += __builtin_bit_cast(float, v[k] << 16);
-                    bsum[2 * k + 1] += __builtin_bit_cast(float, v[k] & 0xffff0000u);
+                for (int k = 0; k < 2; ++k) {
+                    lo[2 * k] += half_bf16(v[k], 0);
+                    lo[2 * k + 1] += half_bf16(v[k], 1);
+                    hi[2 * k] += half_bf16(v[2 + k], 0);
+                    hi[2 * k + 1] += half_bf16(v[2 + k], 1);
                 }
             }
+            bsum[0][tid] = lo;
+            bsum[1][tid] = hi;
         }
+        // the other halves, kept out of the loop-invariant registers
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+            asm volatile("" : "+v"(xa[dx]));
+        // (bit 1 of tq's turn, as below, is clear)
+        const int xo[3] = {xa[0] + 16, xa[1] ^ 16, xa[2] ^ 16};
         // dZ fragments of both k steps (rows 2 wv + kk), both 16-channel halves
         bf16x8 A[2][2];
 #pragma unroll
@@ -1247,29 +1267,42 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
                 const uint16_t *p = Zs + za + kk * WH_TW * WH_PZ;
                 A[kk][u] = tr_fragment(p + 16 * u, p + 4 * WH_PZ + 16 * (1 - u));
             }
+        // Input fragment f = 8 dx + 4 v + rr: halo rows 2 wv + rr, rr = kk +
+        // dy. It serves (dy, kk) = (rr, 0) and (rr - 1, 1), and is read
+        // AHEAD fragments early: the group barriers hold the schedule to
+        // that (left to itself the compiler reads each right before its use).
+        constexpr int AHEAD = 2, MFMA = 0x8, LDS_READ = 0x100;
+        bf16x8 B[AHEAD + 1];
+        auto fragment = [&](int f) {
+            const int dx = f / 8, v = f / 4 % 2, rr = f % 4;
+            B[f % (AHEAD + 1)] = tr_fragment(Xs + (v ? xo[dx] : xa[dx]) + rr * WH_HW * WH_PX,
+                                             Xs + (v ? xa[dx] : xo[dx]) + (rr * WH_HW + 4) * WH_PX);
+        };
 #pragma unroll
-        for (int dx = 0; dx < 3; ++dx) {
-            // the other half, kept out of the loop-invariant registers
-            asm volatile("" : "+v"(xa[dx]));
-            const int half[2] = {xa[dx], xa[dx] ^ 16};
+        for (int f = 0; f < AHEAD; ++f)
+            fragment(f);
+        __builtin_amdgcn_sched_group_barrier(LDS_READ, 8 + 2 * AHEAD, 0);
 #pragma unroll
-            for (int v = 0; v < 2; ++v) {
-                // halo rows 2 wv + rr, rr = kk + dy
-                bf16x8 B[4];
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    B[rr] = tr_fragment(Xs + half[v] + rr * WH_HW * WH_PX,
-                                        Xs + half[1 - v] + (rr * WH_HW + 4) * WH_PX);
-                }
-#pragma unroll
-                for (int dy = 0; dy < 3; ++dy)
-#pragma unroll
-                    for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-                        for (int u = 0; u < 2; ++u)
-                            acc[3 * dy + dx][u][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                A[kk][u], B[kk + dy], acc[3 * dy + dx][u][v], 0, 0, 0);
+        for (int f = 0; f < 24; ++f) {
+            if (f + AHEAD < 24) {
+                fragment(f + AHEAD);
+                __builtin_amdgcn_sched_group_barrier(LDS_READ, 2, 0);
             }
+            const int dx = f / 8, v = f / 4 % 2, rr = f % 4;
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk) {
+                const int dy = rr - kk;
+                if (dy < 0 || dy > 2)
+                    continue;
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    acc[3 * dy + dx][u][v] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        A[kk][u], B[f % (AHEAD + 1)], acc[3 * dy + dx][u][v], 0, 0, 0);
+            }
+            if (rr % 3)
+                __builtin_amdgcn_sched_group_barrier(MFMA, 4, 0);
+            else
+                __builtin_amdgcn_sched_group_barrier(MFMA, 2, 0);
         }
         __syncthreads();  // every wavefront is done with the tiles
         if (more)
@@ -1279,86 +1312,52 @@ void conv_wgrad_halo_kernel(WgradHaloArgs a) {
     if (bias_block) {
         // channel 8 (t % 4) + k of thread t: the 64 sums of a channel (the
         // threads t with the same t % 4), added in thread order
-        float *red = reinterpret_cast<float *>(lds);
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            red[k * THREADS + tid] = bsum[k];
         __syncthreads();
         if (tid < 32) {
             const int k = tid & 7, c4 = tid >> 3;  // channel 8 c4 + k
             float b = 0.f;
             for (int s = 0; s < 64; ++s)
-                b += red[k * THREADS + 4 * s + c4];
+                b += bsum[k >> 2][4 * s + c4][k & 3];
             if (oc0 + tid < a.cout)
                 a.part_b[(long long)kb * a.cout + oc0 + tid] = b;
         }
-        __syncthreads();
     }
-    // The four wavefronts' sums, added in LDS in a fixed order,
-    // (w0 + w2) + (w1 + w3), one wavefront's worth (144 values a lane) at a
-    // time; the workgroup then writes its split.
-    float *red = reinterpret_cast<float *>(lds);
-    auto put = [&]() {
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int v = 0; v < 2; ++v)
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
-                        red[(((t * 2 + u) * 2 + v) * 4 + jj) * 64 + lane] = acc[t][u][v][jj];
-    };
-    auto add = [&]() {
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int v = 0; v < 2; ++v)
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
-                        acc[t][u][v][jj] += red[(((t * 2 + u) * 2 + v) * 4 + jj) * 64 + lane];
-    };
-    __syncthreads();  // the tile area is free
-    if (wv == 2)
-        put();
-    __syncthreads();
-    if (wv == 0)
-        add();
-    __syncthreads();
-    if (wv == 3)
-        put();
-    __syncthreads();
-    if (wv == 1)
-        add();
-    __syncthreads();
-    if (wv == 1)
-        put();
-    __syncthreads();
-    if (wv == 0) {
-        add();
-        // the block's sums in LDS as [o][t][i] (32 x 9 x 32), over the
-        // values just read (a wavefront's LDS accesses stay in order)
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int v = 0; v < 2; ++v)
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
-                        red[((16 * u + 4 * g + jj) * 9 + t) * 32 + 16 * v + m] = acc[t][u][v][jj];
-    }
-    __syncthreads();
-    // the workgroup's split, rows of 32 input channels per (output channel, tap)
+    // The four wavefronts' sums, added through LDS in a fixed order,
+    // (w0 + w2) + (w1 + w3), a quarter of each wavefront's values at a time;
+    // the threads that add them write them to the workgroup's split (runs of
+    // 16 input channels per output channel and tap).
+    f32x4 *red = reinterpret_cast<f32x4 *>(lds);  // [wavefront][9][lane]
     const long long count = (long long)a.cout * 9 * a.cin;
-    float *part = a.part + (long long)kb * count;
-    for (int e = tid; e < 32 * 9 * 32; e += THREADS) {
-        const int o = e / 288, r = e - o * 288;
-        const int t = r >> 5, i = r & 31;
-        if (oc0 + o < a.cout && ic0 + i < a.cin)
-            part[((long long)(oc0 + o) * 9 + t) * a.cin + ic0 + i] = red[e];
+    const __amdgpu_buffer_rsrc_t pr = __builtin_amdgcn_make_buffer_rsrc(
+        a.part + (long long)kb * count, (short)0, (int)(count * 4), BUF_FORMAT_WORD);
+#pragma unroll
+    for (int quarter = 0; quarter < 4; ++quarter) {
+        __syncthreads();  // the tile area is free
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const int q = 9 * quarter + j;
+            red[(wv * 9 + j) * 64 + lane] = acc[q >> 2][q >> 1 & 1][q & 1];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int e = tid + THREADS * k;
+            if (e >= 9 * 64)
+                break;  // wavefront-uniform
+            const int q = 9 * quarter + (e >> 6), l = e & 63;
+            const f32x4 w = (red[e] + red[2 * 576 + e]) + (red[576 + e] + red[3 * 576 + e]);
+            const int o = oc0 + 16 * (q >> 1 & 1) + 4 * (l >> 4), i = ic0 + 16 * (q & 1) + (l & 15);
+            const unsigned off = (unsigned)(((o * 9 + (q >> 2)) * a.cin + i) * 4);
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const float value = w[jj];
+                __builtin_amdgcn_raw_buffer_store_b32(
+                    __builtin_bit_cast(unsigned, value), pr,
+                    o + jj < a.cout && i < a.cin ? off + (unsigned)(jj * 9 * a.cin * 4)
+                                                 : OUT_OF_RANGE,
+                    0, 0);
+            }
+        }
     }
 }
 
