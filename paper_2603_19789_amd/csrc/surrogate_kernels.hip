@@ -1068,10 +1068,11 @@ __global__ __launch_bounds__(THREADS) void conv_wgrad_kernel(WgradArgs a) {
 // pixels, 32 -> 32 channels: 41 us with fragments read right before their use
 // and the wavefronts' sums added one wavefront at a time, 36 now (134 MB: 26
 // us at the rate of a copy); 192 -> 64 channels of 128^2 pixels 88 us, now 83
-// (58 GFLOP: 47 us at the rate of a large matrix product). The workgroups of input block 0 also sum
-// the dZ tile per output channel (the bias gradient): thread (pixel group
-// s, channels 8 j .. 8 j + 7) over pixels s, s + 64, s + 128, s + 192 of
-// every tile; the 64 sums of a channel are then added in order.
+// (58 GFLOP: 47 us at the rate of a large matrix product). The workgroups of
+// input block 0 also sum the dZ tile per output channel (the bias gradient):
+// thread (pixel group s, channels 8 j .. 8 j + 7) over pixels s, s + 64,
+// s + 128, s + 192 of every tile; the 64 sums of a channel are then added in
+// order.
 constexpr int WH_TH = 8, WH_TW = 32;     // pixel tile
 constexpr int WH_HW = WH_TW + 2;         // halo tile columns
 constexpr int WH_HPIX = (WH_TH + 2) * WH_HW;
