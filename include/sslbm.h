@@ -303,7 +303,9 @@ void sslbm_destroy(sslbm_ctx *c);
  *   sslbm_run_checkpointed: as sslbm_run (result in rho, scratch clobbered),
  *       and stores the state at steps 0, every, 2 every, ... into
  *       checkpoints, a device buffer of sslbm_checkpoint_count states. Each
- *       segment runs straight into the next checkpoint, and every = 2 takes
+ *       segment runs straight into the next checkpoint (in one pass, scratch
+ *       unused, for every up to the deepest march of the type, 5 in FP64 and
+ *       8 in FP32, except where sslbm_run takes tiles), and every = 2 takes
  *       two segments per pass; the reverse sweep then recomputes nothing, at
  *       the cost of nsteps / 2 stored states (1024^2 FP64 x 2000 steps:
  *       42 GB).

@@ -159,7 +159,14 @@ sslbm_status run_pass(sslbm_ctx *c, const void *in, void *out, int k, hipStream_
 sslbm_status run_segment(sslbm_ctx *c, const void *src, void *dst, void *tmp0, void *tmp1,
                          long long n, hipStream_t s) {
     const TilePlan tiles = run_tiles(c, n);
-    const int K = tiles.rows ? tiles.depth : resolve(c).steps_per_pass;
+    // A march takes a segment that one wavefront can hold in one pass,
+    // whatever the context's steps per pass: a state less through HBM each way
+    // than in two passes (FP32 4096^2 every 8 steps: 2247 us for 64 steps, 2741
+    // in passes of four; FP64 with a diffusing D every 5: 2827 us for 40 steps
+    // although that kernel spills, 5449 in passes of three and two).
+    const int K = tiles.rows                                   ? tiles.depth
+                  : n <= sslbm::march_max_depth(c->dtype, 1) ? (int)n
+                                                               : resolve(c).steps_per_pass;
     const long long count = (n + K - 1) / K, longer = n % count;
     const int base = (int)(n / count);
     for (long long i = 0; i < count; ++i) {

@@ -56,7 +56,8 @@ PassPlan plan_passes(long long nsteps, int K);
 // One pass of k steps (1 <= k <= the register limit), in -> out, with the
 // context's pass shape (SSLBM status code).
 sslbm_status run_pass(sslbm_ctx *c, const void *in, void *out, int k, hipStream_t s);
-// n >= 1 steps src -> dst in the fewest passes, through tmp0 and tmp1 (states of
+// n >= 1 steps src -> dst in the fewest passes (one where a march can hold
+// them), through tmp0 and tmp1 (states of
 // their own; src, dst, tmp0 and tmp1 do not overlap, except that tmp1 may be dst).
 sslbm_status run_segment(sslbm_ctx *c, const void *src, void *dst, void *tmp0, void *tmp1,
                          long long n, hipStream_t s);

@@ -1,0 +1,27 @@
+"""Which launches calls of the library make (tests/launches.py; no GPU)."""
+import pytest
+
+from launches import record
+
+
+@pytest.mark.parametrize("dtype,d_dead,every", [("f32", 0.0, 7), ("f32", 0.0, 8), ("f32", 3e-3, 8),
+                                                ("f64", 3e-3, 5), ("f64", 0.0, 5)])
+@pytest.mark.parametrize("shape", [(0, 0, 0), (1, 0, 0), (2, 40, 2)])
+def test_a_segment_that_fits_a_march_is_one_pass(dtype, d_dead, every, shape):
+    """Up to the deepest march, recorded runs write each segment straight into
+    the next checkpoint in one pass, whatever the context's steps per pass."""
+    if shape[2] == 2 and dtype == "f64":
+        shape = (2, 40, 1)
+    result = record(f'''
+h = context(1536, 1100, {dtype!r}, {d_dead})
+assert lib.sslbm_set_launch(h, ctypes.byref(Launch(*{shape}))) == 0
+steps = 3 * {every} + 2
+one = passes(lambda: lib.sslbm_run_checkpointed(h, rho, scratch, steps, {every}, extra, None))
+result = [one, [l[4:] for l in launched()]]
+''')
+    kinds, ends = result
+    assert [k[:2] for k in kinds] == [["copy", None]] + 3 * [["march", every]] + [["march", 2]]
+    scratch = 2 << 40
+    assert all(scratch not in e for e in ends)  # scratch is not touched
+    assert all(ends[i][1] == ends[i + 1][0] for i in range(1, 4))
+    assert ends[-1][1] == 1 << 40  # the last segment ends in rho
