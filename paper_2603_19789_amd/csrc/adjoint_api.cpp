@@ -195,15 +195,22 @@ sslbm_status sslbm_run_checkpointed(sslbm_ctx *c, void *rho, void *scratch, long
     auto slot = [&](long long k) -> void * {
         return k < count ? static_cast<void *>(cp + (size_t)k * bytes) : rho;
     };
+    // segments are `every` steps long, the last one may be shorter: two shapes
+    // for the whole call (working one out costs 1 to 3 us of host time, a
+    // quarter of a segment of one step on a small grid)
+    const long long last = nsteps - (count - 1) * every;
+    const sslbm::SegmentShape full = sslbm::segment_shape(c, every);
+    const sslbm::SegmentShape tail = last < every ? sslbm::segment_shape(c, last) : full;
     for (long long k = 0; k < count;) {
-        const long long n = nsteps - k * every < every ? nsteps - k * every : every;
+        const long long n = k == count - 1 ? last : every;
         if (every == 2 && n == 2 && k + 1 < count && nsteps - (k + 1) * every >= 2) {
             // two segments in one pass of 4 steps, the state after 2 steps
             // written on the way
             st = sslbm::run_pass_mid2(c, slot(k), slot(k + 1), slot(k + 2), s);
             k += 2;
         } else {
-            st = sslbm::run_segment(c, slot(k), slot(k + 1), scratch, rho, n, s);
+            st = sslbm::run_segment(c, n < every ? tail : full, slot(k), slot(k + 1), scratch, rho, n,
+                                    s);
             k += 1;
         }
         if (st != SSLBM_OK)

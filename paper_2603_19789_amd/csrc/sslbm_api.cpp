@@ -101,11 +101,11 @@ bool automatic(const sslbm_launch &r) {
 
 // Tiles of a run of nsteps: none (rows = 0) where the caller has chosen a
 // march shape or the grid is too large for them.
-sslbm::TilePlan run_tiles(const sslbm_ctx *c, long long nsteps) {
+sslbm::TilePlan run_tiles(const sslbm_ctx *c, long long nsteps, bool fewest = false) {
     if (!automatic(c->launch))
         return sslbm::TilePlan();
     const sslbm::GridSize size{c->nx, c->ny, 1};
-    return sslbm::tile_plan(c->dtype, &size, 1, nsteps);
+    return sslbm::tile_plan(c->dtype, &size, 1, nsteps, fewest);
 }
 
 // March shape of a pass: requested fields, automatic ones filled in.
@@ -156,28 +156,32 @@ sslbm_status run_pass(sslbm_ctx *c, const void *in, void *out, int k, hipStream_
                                       shape_for(c, k, in, out), s));
 }
 
-sslbm_status run_segment(sslbm_ctx *c, const void *src, void *dst, void *tmp0, void *tmp1,
-                         long long n, hipStream_t s) {
-    const TilePlan tiles = run_tiles(c, n);
+SegmentShape segment_shape(const sslbm_ctx *c, long long n) {
+    SegmentShape shape;
+    shape.tiles = run_tiles(c, n, true);
     // A march takes a segment that one wavefront can hold in one pass,
     // whatever the context's steps per pass: a state less through HBM each way
     // than in two passes (FP32 4096^2 every 8 steps: 2247 us for 64 steps, 2741
     // in passes of four; FP64 with a diffusing D every 5: 2827 us for 40 steps
     // although that kernel spills, 5449 in passes of three and two).
-    const int K = tiles.rows                                   ? tiles.depth
-                  : n <= sslbm::march_max_depth(c->dtype, 1) ? (int)n
-                                                               : resolve(c).steps_per_pass;
-    const long long count = (n + K - 1) / K, longer = n % count;
-    const int base = (int)(n / count);
-    for (long long i = 0; i < count; ++i) {
-        const int k = i < longer ? base + 1 : base;
+    shape.depth = shape.tiles.rows                      ? shape.tiles.depth
+                  : n <= march_max_depth(c->dtype, 1) ? (int)n
+                                                        : resolve(c).steps_per_pass;
+    return shape;
+}
+
+sslbm_status run_segment(sslbm_ctx *c, const SegmentShape &shape, const void *src, void *dst,
+                         void *tmp0, void *tmp1, long long n, hipStream_t s) {
+    const PassPlan plan = fewest_passes(n, shape.depth);
+    for (long long i = 0; i < plan.count; ++i) {
+        const int k = plan.steps(i);
         // the pass before the last one writes tmp0, so the last may read it
         // and write dst = tmp1
-        void *out = i == count - 1 ? dst : ((count - 2 - i) % 2 == 0 ? tmp0 : tmp1);
+        void *out = i == plan.count - 1 ? dst : ((plan.count - 2 - i) % 2 == 0 ? tmp0 : tmp1);
         const sslbm_status st =
-            tiles.rows ? hip_status(c, launch_tile(c->dtype, src, out, grid_of(c), c->coef, k,
-                                                   tiles.rows, s))
-                       : run_pass(c, src, out, k, s);
+            shape.tiles.rows ? hip_status(c, launch_tile(c->dtype, src, out, grid_of(c), c->coef,
+                                                         k, shape.tiles.rows, s))
+                             : run_pass(c, src, out, k, s);
         if (st != SSLBM_OK)
             return st;
         src = out;
@@ -238,17 +242,25 @@ sslbm_status derive_coef(const sslbm_params *p, StepCoef *k) {
     return SSLBM_OK;
 }
 
-PassPlan plan_passes(long long nsteps, int K) {
+PassPlan fewest_passes(long long nsteps, int K) {
     PassPlan p;
     if (nsteps <= 0 || K < 1)
         return p;
     p.count = (nsteps + K - 1) / K;
-    // one more pass only while every pass keeps at least one step (K = 1 and
-    // an odd nsteps stay odd: the run then ends with a copy)
-    if (p.count % 2 == 1 && p.count < nsteps)
-        ++p.count;
     p.base = (int)(nsteps / p.count);
     p.longer = nsteps - (long long)p.base * p.count;
+    return p;
+}
+
+PassPlan plan_passes(long long nsteps, int K) {
+    PassPlan p = fewest_passes(nsteps, K);
+    // one more pass only while every pass keeps at least one step (K = 1 and
+    // an odd nsteps stay odd: the run then ends with a copy)
+    if (p.count % 2 == 1 && p.count < nsteps) {
+        ++p.count;
+        p.base = (int)(nsteps / p.count);
+        p.longer = nsteps - (long long)p.base * p.count;
+    }
     return p;
 }
 

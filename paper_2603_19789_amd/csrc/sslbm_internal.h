@@ -52,15 +52,12 @@ struct PassPlan {
     int steps(long long i) const { return i < longer ? base + 1 : base; }
 };
 PassPlan plan_passes(long long nsteps, int K);
+// The same without a pass more to make their number even.
+PassPlan fewest_passes(long long nsteps, int K);
 
 // One pass of k steps (1 <= k <= the register limit), in -> out, with the
 // context's pass shape (SSLBM status code).
 sslbm_status run_pass(sslbm_ctx *c, const void *in, void *out, int k, hipStream_t s);
-// n >= 1 steps src -> dst in the fewest passes (one where a march can hold
-// them), through tmp0 and tmp1 (states of
-// their own; src, dst, tmp0 and tmp1 do not overlap, except that tmp1 may be dst).
-sslbm_status run_segment(sslbm_ctx *c, const void *src, void *dst, void *tmp0, void *tmp1,
-                         long long n, hipStream_t s);
 // One pass of 4 steps in -> out writing the state after 2 steps to mid.
 sslbm_status run_pass_mid2(sslbm_ctx *c, const void *in, void *mid, void *out, hipStream_t s);
 
@@ -97,11 +94,26 @@ struct GridSize {
     int nx, ny;
     int count;  // grids of this size
 };
-TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps);
+// The passes of such a run are plan_passes' (an even number), or with
+// fewest = true as few as the depth allows.
+TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps, bool fewest = false);
 long long tile_count(int nx, int ny, int R, int K);
 // K steps in -> out (no overlap) with R rows a lane.
 hipError_t launch_tile(int dtype, const void *in, void *out, const GridDesc &g, const StepCoef &k,
                        int K, int R, hipStream_t s);
+
+// ---- segments of a recorded run (sslbm_api.cpp) ---------------------------
+// n >= 1 steps from one buffer to another: the passes' shape, which a caller
+// with many segments of the same length works out once, and the segment.
+struct SegmentShape {
+    TilePlan tiles;  // rows = 0: a march
+    int depth = 0;   // most steps a pass
+};
+SegmentShape segment_shape(const sslbm_ctx *c, long long n);
+// src -> dst in the fewest passes, through tmp0 and tmp1 (states of their own;
+// src, dst, tmp0 and tmp1 do not overlap, except that tmp1 may be dst).
+sslbm_status run_segment(sslbm_ctx *c, const SegmentShape &shape, const void *src, void *dst,
+                         void *tmp0, void *tmp1, long long n, hipStream_t s);
 
 // ---- launchers (bgk_kernels.hip) ----------------------------------------
 hipError_t launch_bgk_init(int dtype, const void *rho, void *f, void *rhoD, const GridDesc &g,

@@ -42,19 +42,17 @@ int compute_units() {
 // exact rows, per SIMD) and the loads and stores, the last two once for every
 // round of tiles. The shape it prefers was the fastest measured one, or within
 // 1% of it, at every size in the range.
-double pass_us(int dtype, int R, int K, long long tiles, int cus) {
+// `rows` is the sum over the steps.
+double pass_us(int dtype, int R, int K, int rows, long long tiles, int cus) {
     const bool f32 = dtype == SSLBM_F32;
     const double rounds = (double)((tiles + cus - 1) / cus);
-    double rows = 0.0;
-    for (int s = 1; s <= K; ++s)
-        rows += (TILE_WAVES - 2 * (s / R)) * R / 4;
     return f32 ? 1.38 + 0.310 * K + rounds * (0.0604 * rows + 0.768 * R)
                : 1.46 + 0.213 * K + rounds * (0.1274 * rows + 1.463 * R);
 }
 
 }  // namespace
 
-TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps) {
+TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps, bool fewest) {
     TilePlan best;
     // Up to where the march has enough rows for every SIMD, it waits for
     // memory (FP32 1152^2: 3.64 against 3.83 us a step, 1280^2 4.27 against
@@ -70,21 +68,29 @@ TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps) {
     const int *rows = dtype == SSLBM_F32 ? F32_ROWS : F64_ROWS;
     const int heights = dtype == SSLBM_F32 ? 5 : 3;
     double best_us = 0.0;
-    for (int j = 0; j < heights; ++j)
-        for (int K = 1; K <= TILE_MAX_DEPTH && 2 * K < TILE_WAVES * rows[j]; ++K) {
+    // a pass takes no more steps than the run has
+    const int deepest = nsteps < TILE_MAX_DEPTH ? (int)nsteps : TILE_MAX_DEPTH;
+    for (int j = 0; j < heights; ++j) {
+        const int R = rows[j];
+        int busy[TILE_MAX_DEPTH + 1] = {};  // rows per SIMD of a pass of so many steps
+        for (int s = 1; s <= deepest; ++s)
+            busy[s] = busy[s - 1] + (TILE_WAVES - 2 * (s / R)) * R / 4;
+        for (int K = 1; K <= deepest && 2 * K < TILE_WAVES * R; ++K) {
             long long tiles = 0;
             for (int i = 0; i < n; ++i)
-                tiles += tile_count(sizes[i].nx, sizes[i].ny, rows[j], K) * sizes[i].count;
+                tiles += tile_count(sizes[i].nx, sizes[i].ny, R, K) * sizes[i].count;
             if (tiles > 0x7fffffffll)
                 continue;
-            const PassPlan p = plan_passes(nsteps, K);
-            const double us = (double)p.count * pass_us(dtype, rows[j], p.steps(0), tiles, cus);
+            const PassPlan p = fewest ? fewest_passes(nsteps, K) : plan_passes(nsteps, K);
+            const int k = p.steps(0);
+            const double us = (double)p.count * pass_us(dtype, R, k, busy[k], tiles, cus);
             if (best.rows == 0 || us < best_us) {
                 best_us = us;
-                best.rows = rows[j];
+                best.rows = R;
                 best.depth = K;
             }
         }
+    }
     return best;
 }
 

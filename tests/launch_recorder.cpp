@@ -31,6 +31,7 @@ double now_ms = 0.0;
 bool device = true;  // device queries succeed
 std::map<hipEvent_t, double> stamps;
 int last_error = 0;
+int queries = 0;  // of the current device
 
 struct Config {
     dim3 grid, block;
@@ -54,6 +55,7 @@ void rec_clear() { records.clear(); }
 void rec_price(const char *part, double ms) { prices.emplace_back(part, ms); }
 void rec_device(int there) { device = there != 0; }
 int rec_last_error() { return last_error; }
+int rec_queries() { return std::exchange(queries, 0); }
 // The 32-bit word at byte offset `at` of argument a of launch i.
 int rec_arg(int i, int a, int at) {
     int v = 0;
@@ -137,6 +139,7 @@ hipError_t hipFree(void *p) {
 }
 hipError_t hipGetDevice(int *d) {
     *d = 0;
+    ++queries;
     if (!device)
         last_error = hipErrorNoDevice;
     return device ? hipSuccess : hipErrorNoDevice;

@@ -25,3 +25,24 @@ result = [one, [l[4:] for l in launched()]]
     assert all(scratch not in e for e in ends)  # scratch is not touched
     assert all(ends[i][1] == ends[i + 1][0] for i in range(1, 4))
     assert ends[-1][1] == 1 << 40  # the last segment ends in rho
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("every", [1, 2, 3, 4, 5, 7, 11, 23])
+def test_tile_segments_take_the_fewest_passes(dtype, every):
+    """On small grids too a segment needs no even number of passes, and the
+    passes' shape is worked out once a call, not once a segment."""
+    result = record(f'''
+h = context(128, 128, {dtype!r})
+kinds = passes(lambda: lib.sslbm_run_checkpointed(h, rho, scratch, 40 * {every}, {every}, extra,
+                                                  None))
+result = [kinds, rec.rec_queries()]
+''')
+    kinds, queries = result
+    if every == 2:
+        assert [k[0] for k in kinds] == ["copy"] + 20 * ["mid"]
+    else:
+        assert {k[0] for k in kinds[1:]} == {"tile"}
+        # FP64 tiles of one row a lane hold at most 7 steps
+        assert (len(kinds) - 1) % 40 == 0 and (len(kinds) - 1) // 40 <= -(-every // 7)
+        assert queries <= 4
