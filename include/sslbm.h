@@ -154,7 +154,8 @@ int sslbm_get_blocking(const sslbm_ctx *c);
  * sslbm_get_launch reports the shape sslbm_run uses (automatic fields resolved).
  * With every field automatic, sslbm_run takes grids of at most 1.4 million
  * cells in FP32 (0.45 million in FP64) in passes of tiles held in registers
- * instead, of up to 16 steps; the shape reported is then the one that passes
+ * instead, of up to 16 steps, unless it estimates the march to be faster (as on
+ * long grids of a few rows or columns); the shape reported is then the one that passes
  * of the march would have. sslbm_plan_run reports the passes either way.
  */
 typedef struct {

@@ -89,6 +89,7 @@ struct sslbm_ensemble {
     int device = -1;
     void *insts = nullptr;    // device instance table
     int *lds_list = nullptr;  // device list of the on-chip instances
+    bool tiles_tuned = false;  // automatic shapes because tiles were the fastest when timed
     std::vector<sslbm::GridSize> march_sizes;  // distinct sizes of the march classes' grids
     // tables of a chain's passes: {steps, columns per lane, then class and rows
     // per wavefront of each march class}, or {steps, 0, rows a lane, classes}
@@ -293,6 +294,30 @@ struct Chain {
     int depth() const { return tiles.rows ? tiles.depth : K; }
 };
 
+// Estimated time of a step by a chain's marches.
+double march_step_us(const sslbm_ensemble *e, const Chain &ch) {
+    const int w = sslbm::strip_width(ch.K, ch.V);
+    long long waves = 0;
+    int rows = 0;
+    for (size_t i = 0; i < ch.classes.size(); ++i) {
+        waves += count_tiles(e->classes[ch.classes[i]].sizes, w, ch.H[i]);
+        rows = std::max(rows, ch.H[i]);
+    }
+    return sslbm::march_us(e->dtype, ch.K, ch.V, rows, waves) / ch.K;
+}
+
+// Tiles of a chain whose shapes are all automatic: as for a single grid, none
+// where its grids are too large for them or the march is estimated to be faster.
+sslbm::TilePlan chain_tiles(const sslbm_ensemble *e, const std::vector<sslbm::GridSize> &sizes,
+                            const Chain &ch, long long nsteps) {
+    const int n = (int)sizes.size();
+    const sslbm::TilePlan tiles = sslbm::tile_plan(e->dtype, sizes.data(), n, nsteps);
+    if (tiles.rows == 0 || tiles.few || e->tiles_tuned ||
+        sslbm::tiles_pay(e->dtype, sizes.data(), n, march_step_us(e, ch)))
+        return tiles;
+    return sslbm::TilePlan();
+}
+
 // The march chains of a run of nsteps.
 std::vector<Chain> march_chains(const sslbm_ensemble *e, long long nsteps, bool pairs_ok) {
     std::vector<Chain> out;
@@ -314,17 +339,15 @@ std::vector<Chain> march_chains(const sslbm_ensemble *e, long long nsteps, bool 
     }
     if (out.empty())
         return out;
-    sslbm::TilePlan tiles;
-    if (automatic)
-        tiles = sslbm::tile_plan(e->dtype, e->march_sizes.data(), (int)e->march_sizes.size(),
-                                 nsteps);
-    if (tiles.rows || alike) {
+    // automatic shapes are alike
+    if (alike) {
         for (size_t i = 1; i < out.size(); ++i) {
             out[0].classes.push_back(out[i].classes[0]);
             out[0].H.push_back(out[i].H[0]);
         }
         out.resize(1);
-        out[0].tiles = tiles;
+        if (automatic)
+            out[0].tiles = chain_tiles(e, e->march_sizes, out[0], nsteps);
     }
     return out;
 }
@@ -340,7 +363,7 @@ Chain class_chain(const sslbm_ensemble *e, int c, long long nsteps, bool pairs_o
     ch.H = {r.rows_per_wave};
     if (cl.launch.steps_per_pass == 0 && cl.launch.rows_per_wave == 0 &&
         cl.launch.cols_per_lane == 0)
-        ch.tiles = sslbm::tile_plan(e->dtype, cl.sizes.data(), (int)cl.sizes.size(), nsteps);
+        ch.tiles = chain_tiles(e, cl.sizes, ch, nsteps);
     return ch;
 }
 
@@ -624,12 +647,15 @@ sslbm_status tune_classes(sslbm_ensemble *e, const void *rho, void *scratch, boo
             keep.push_back(cl.launch);
             cl.launch = sslbm_launch{};
         }
+        e->tiles_tuned = true;
         const double rate = joint_rate(e, rho, scratch, pairs_ok, t0, t1, &st);
         if (st != SSLBM_OK)
             return st;
-        if (rate <= best)
+        if (rate <= best) {
             for (size_t c = 0; c < e->classes.size(); ++c)
                 e->classes[c].launch = keep[c];
+            e->tiles_tuned = false;
+        }
     }
     return SSLBM_OK;
 }
@@ -777,6 +803,7 @@ sslbm_status sslbm_ensemble_set_class_launch(sslbm_ensemble *e, int cls,
     if (e->classes[cls].on_chip)
         return SSLBM_E_UNSUPPORTED;
     e->classes[cls].launch = *shape;
+    e->tiles_tuned = false;
     drop_graphs(e);
     return SSLBM_OK;
 }
@@ -790,6 +817,7 @@ sslbm_status sslbm_ensemble_set_launch(sslbm_ensemble *e, const sslbm_launch *sh
     for (EnsClass &cl : e->classes)
         if (!cl.on_chip)
             cl.launch = *shape;
+    e->tiles_tuned = false;
     drop_graphs(e);
     return SSLBM_OK;
 }
@@ -919,12 +947,15 @@ sslbm_status sslbm_ensemble_tune(sslbm_ensemble *e, const void *rho, void *scrat
     std::vector<sslbm_launch> saved;
     for (const EnsClass &cl : e->classes)
         saved.push_back(cl.launch);
+    const bool saved_tiles = e->tiles_tuned;
+    e->tiles_tuned = false;
     st = tune_classes(e, rho, scratch, pairs_ok, t0, t1);
     (void)hipEventDestroy(t0);
     (void)hipEventDestroy(t1);
     if (st != SSLBM_OK) {
         for (size_t c = 0; c < e->classes.size(); ++c)
             e->classes[c].launch = saved[c];
+        e->tiles_tuned = saved_tiles;
         return st;
     }
     drop_graphs(e);

@@ -99,15 +99,6 @@ bool automatic(const sslbm_launch &r) {
     return r.steps_per_pass == 0 && r.rows_per_wave == 0 && r.cols_per_lane == 0;
 }
 
-// Tiles of a run of nsteps: none (rows = 0) where the caller has chosen a
-// march shape or the grid is too large for them.
-sslbm::TilePlan run_tiles(const sslbm_ctx *c, long long nsteps, bool fewest = false) {
-    if (!automatic(c->launch))
-        return sslbm::TilePlan();
-    const sslbm::GridSize size{c->nx, c->ny, 1};
-    return sslbm::tile_plan(c->dtype, &size, 1, nsteps, fewest);
-}
-
 // March shape of a pass: requested fields, automatic ones filled in.
 sslbm_launch resolve(const sslbm_ctx *c) {
     sslbm_launch r = automatic(c->launch) ? c->tuned : c->launch;
@@ -127,6 +118,30 @@ sslbm_launch resolve(const sslbm_ctx *c) {
     if (r.rows_per_wave == 0)
         r.rows_per_wave = auto_rows(c, r.steps_per_pass, r.cols_per_lane);
     return r;
+}
+
+// Tiles of a run of nsteps (of a segment: with the fewest passes): none (rows =
+// 0) where the caller has chosen a march shape, the grid is too large for them,
+// or the march is estimated to be faster. That is the case on grids a few cells
+// high, where tiles compute mostly halo rows (60 steps, tiles against march:
+// FP32 70000 x 2 229 and 95 us, FP64 440000 x 1 1567 and 388), on long ones a
+// few cells wide (FP64 1 x 70000: 1026 and 631), and at sizes whose march just
+// fills its wavefronts (FP32 1101^2: 239 and 211). A context that was tuned and
+// is still on automatic shapes takes tiles: they were the faster when timed.
+sslbm::TilePlan run_tiles(const sslbm_ctx *c, long long nsteps, bool fewest = false) {
+    if (!automatic(c->launch))
+        return sslbm::TilePlan();
+    const sslbm::GridSize size{c->nx, c->ny, 1};
+    const sslbm::TilePlan tiles = sslbm::tile_plan(c->dtype, &size, 1, nsteps, fewest);
+    if (tiles.rows == 0 || tiles.few || c->tuned.steps_per_pass > 0)
+        return tiles;
+    const sslbm_launch r = resolve(c);
+    const int K = r.steps_per_pass, V = c->nx % 2 == 0 ? r.cols_per_lane : 1;
+    const int rows = auto_rows(c, K, V), w = sslbm::strip_width(K, V);
+    const long long waves =
+        (long long)((c->nx + w - 1) / w) * ((c->ny + rows - 1) / rows);
+    const double march = sslbm::march_us(c->dtype, K, V, rows, waves) / K;
+    return sslbm::tiles_pay(c->dtype, &size, 1, march) ? tiles : sslbm::TilePlan();
 }
 
 // Shape of one pass of k steps (the last pass of a run may be shorter). Two

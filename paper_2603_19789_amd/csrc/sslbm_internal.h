@@ -89,6 +89,8 @@ constexpr int TILE_MAX_DEPTH = 16;
 struct TilePlan {
     int rows = 0;
     int depth = 0;
+    double us = 0.0;   // estimated time of the run
+    bool few = false;  // so few tiles that half of the CUs hold them
 };
 struct GridSize {
     int nx, ny;
@@ -98,6 +100,15 @@ struct GridSize {
 // fewest = true as few as the depth allows.
 TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps, bool fewest = false);
 long long tile_count(int nx, int ny, int R, int K);
+// Estimated time in us of one march pass of K steps by `waves` wavefronts of H
+// rows, on grids small enough for tiles.
+double march_us(int dtype, int K, int cols_per_lane, int H, long long waves);
+// Whether a long run on n grid sizes is faster with tiles than with marches of
+// march_us a step (asked where tiles are not few: runs of every length then take
+// the same kind of pass).
+bool tiles_pay(int dtype, const GridSize *sizes, int n, double march_us);
+// Compute units of the current device (256 where it cannot be asked).
+int compute_units();
 // K steps in -> out (no overlap) with R rows a lane.
 hipError_t launch_tile(int dtype, const void *in, void *out, const GridDesc &g, const StepCoef &k,
                        int K, int R, hipStream_t s);

@@ -23,8 +23,6 @@ long long tile_count(int nx, int ny, int R, int K) {
     return (long long)((nx + w - 1) / w) * ((ny + h - 1) / h);
 }
 
-namespace {
-
 int compute_units() {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -36,27 +34,40 @@ int compute_units() {
     return cus;
 }
 
-// Time of one pass in us, from a fit to 1000 measured passes (48^2 to 1024^2,
-// every R below, 1 to 17 steps; 6% rms in FP32, 12% in FP64): the launch, a
-// step's barrier, a step's vector work (rows of the wavefronts that still have
-// exact rows, per SIMD) and the loads and stores, the last two once for every
-// round of tiles. The shape it prefers was the fastest measured one, or within
-// 1% of it, at every size in the range.
-// `rows` is the sum over the steps.
-double pass_us(int dtype, int R, int K, int rows, long long tiles, int cus) {
-    const bool f32 = dtype == SSLBM_F32;
+// Time of one pass in us, from a fit to 3000 measured passes (48^2 to 1180^2
+// and grids 1 to 200 cells wide or high, every R below, 1 to 15 steps; 8% rms):
+// the launch, a step's barrier, for every round of tiles its start and a step's
+// vector work (`rows`: rows of the wavefronts that still have exact rows, per
+// SIMD, summed over the steps), and the loads and stores of the tiles that run
+// at once. Over those sizes the shape it prefers is within 2% of the fastest
+// measured one on the mean.
+static double pass_us(int dtype, int R, int K, int rows, long long tiles, int cus) {
     const double rounds = (double)((tiles + cus - 1) / cus);
-    return f32 ? 1.38 + 0.310 * K + rounds * (0.0604 * rows + 0.768 * R)
-               : 1.46 + 0.213 * K + rounds * (0.1274 * rows + 1.463 * R);
+    const double filled = tiles < cus ? (double)tiles / cus : 1.0;
+    return dtype == SSLBM_F32
+               ? 3.06 + 0.126 * K + rounds * (0.643 + 0.0720 * rows) + 0.429 * filled * R
+               : 1.58 + 0.0644 * K + rounds * (2.01 + 0.1556 * rows) + 0.494 * filled * R;
 }
 
-}  // namespace
+// From a fit to 640 measured passes (grids and ensembles of up to 4 million
+// cells, 1 to 10 wavefronts a SIMD; FP32 5% rms with one column a lane and 6%
+// with two, FP64 9%): a wavefront computes H rows of every level and half of
+// 2K more while they fill, and the wavefronts of a SIMD share its issue slots.
+double march_us(int dtype, int K, int cols_per_lane, int H, long long waves) {
+    const int simds = 4 * compute_units();
+    const double rows = (double)H * K + (double)K * K;
+    const double share = (double)((waves + simds - 1) / simds);
+    if (dtype == SSLBM_F64)
+        return 3.29 + rows * (0.0123 + 0.1335 * share);
+    return cols_per_lane == 2 ? 4.61 + rows * (0.0697 + 0.1032 * share)
+                              : 2.82 + rows * (0.0574 + 0.0547 * share);
+}
 
 TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps, bool fewest) {
     TilePlan best;
-    // Up to where the march has enough rows for every SIMD, it waits for
-    // memory (FP32 1152^2: 3.64 against 3.83 us a step, 1280^2 4.27 against
-    // 4.2; FP64 640^2: 2.55 against 2.80, 704^2 3.58 against 3.21).
+    // Beyond this many cells the march has enough rows for every SIMD (FP32
+    // 1180^2: tiles 3.64 us a step, march 4.42, 1280^2 4.27 against 4.2; FP64
+    // 670^2: 2.8 against 2.95, 704^2 3.58 against 3.21).
     const long long most = dtype == SSLBM_F32 ? 1400000 : 450000;
     long long cells = 0;
     for (int i = 0; i < n; ++i)
@@ -67,7 +78,6 @@ TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps, bo
     constexpr int F32_ROWS[] = {2, 3, 4, 5, 7}, F64_ROWS[] = {1, 2, 3};
     const int *rows = dtype == SSLBM_F32 ? F32_ROWS : F64_ROWS;
     const int heights = dtype == SSLBM_F32 ? 5 : 3;
-    double best_us = 0.0;
     // a pass takes no more steps than the run has
     const int deepest = nsteps < TILE_MAX_DEPTH ? (int)nsteps : TILE_MAX_DEPTH;
     for (int j = 0; j < heights; ++j) {
@@ -84,14 +94,20 @@ TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps, bo
             const PassPlan p = fewest ? fewest_passes(nsteps, K) : plan_passes(nsteps, K);
             const int k = p.steps(0);
             const double us = (double)p.count * pass_us(dtype, R, k, busy[k], tiles, cus);
-            if (best.rows == 0 || us < best_us) {
-                best_us = us;
+            if (best.rows == 0 || us < best.us) {
                 best.rows = R;
                 best.depth = K;
+                best.us = us;
+                best.few = tiles <= cus / 2;
             }
         }
     }
     return best;
+}
+
+bool tiles_pay(int dtype, const GridSize *sizes, int n, double march_us) {
+    constexpr int LONG = 1000;
+    return tile_plan(dtype, sizes, n, LONG).us <= 1.05 * LONG * march_us;
 }
 
 template <typename T, int R, bool DD>

@@ -8,6 +8,7 @@
 #include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
 
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -148,9 +149,18 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) {
     *v = 256;
     return device ? hipSuccess : hipErrorNoDevice;
 }
-hipError_t hipFuncGetAttributes(hipFuncAttributes *a, const void *) {
+// Registers of a march kernel, near enough for its wavefronts per SIMD.
+hipError_t hipFuncGetAttributes(hipFuncAttributes *a, const void *f) {
     std::memset(a, 0, sizeof *a);
-    a->numRegs = 240;  // two wavefronts a SIMD
+    char type[8] = "";
+    int K = 0, V = 0;
+    const std::string &name = names[f];
+    const size_t at = name.find('<');
+    if (at == std::string::npos ||
+        std::sscanf(name.c_str() + at, "<%7[a-z], %d, %*[a-z], %d>", type, &K, &V) != 3)
+        return hipErrorInvalidValue;
+    const int words = type[0] == 'd' ? 2 : 1, regs = words * V * (15 * K + 35);
+    a->numRegs = regs < 256 ? regs : 256;
     return hipSuccess;
 }
 hipError_t hipGetLastError() {

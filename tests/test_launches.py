@@ -45,4 +45,39 @@ result = [kinds, rec.rec_queries()]
         assert {k[0] for k in kinds[1:]} == {"tile"}
         # FP64 tiles of one row a lane hold at most 7 steps
         assert (len(kinds) - 1) % 40 == 0 and (len(kinds) - 1) // 40 <= -(-every // 7)
-        assert queries <= 4
+        assert queries < 20  # of the device, one a plan: 40 segments
+
+
+# (nx, ny), kernels of a run: tiles where they are faster, the march on grids
+# a few cells high, long ones a few cells wide, and where it just fills the GPU
+ROUTES = {
+    "f32": [((1, 1), "tile"), ((128, 128), "tile"), ((1024, 1024), "tile"), ((20000, 8), "tile"),
+            ((16, 12500), "tile"), ((64, 6875), "tile"), ((1180, 1180), "tile"),
+            ((262144, 1), "march"), ((70000, 2), "march"), ((131072, 8), "march"),
+            ((1, 440000), "march"), ((1300, 1300), "march")],
+    "f64": [((1, 1), "tile"), ((128, 128), "tile"), ((512, 512), "tile"), ((200, 2000), "tile"),
+            ((12500, 16), "tile"), ((16, 4375), "tile"), ((262144, 1), "march"),
+            ((35000, 2), "march"), ((32768, 8), "march"), ((1, 70000), "march"),
+            ((4, 100000), "march"), ((700, 700), "march")],
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_tiles_only_where_they_are_faster(dtype):
+    """Single grids, and ensembles of one grid too large for LDS."""
+    result = record(f'''
+result = []
+for (nx, ny), want in {ROUTES[dtype]!r}:
+    h = context(nx, ny, {dtype!r})
+    single = {{k[0] for k in passes(lambda: lib.sslbm_run(h, rho, scratch, 60, None))}}
+    many = {{want}}
+    if 5 * nx * ny * {4 if dtype == "f32" else 8} > 81920 and max(nx, ny) <= 65536:
+        e = ensemble([(nx, ny)], {dtype!r})
+        many = {{k[0] for k in passes(lambda: lib.sslbm_ensemble_run(e, rho, scratch, 60, 0, None))}}
+    result.append([nx, ny, sorted(single), sorted(many), want])
+''')
+    bad = [r for r in result if r[2] != [r[4]]]
+    assert not bad, bad
+    # ensembles name their march kernel differently
+    bad = [r for r in result if r[4] == "tile" and r[3] != ["tile"]]
+    assert not bad, bad
