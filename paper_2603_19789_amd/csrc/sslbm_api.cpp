@@ -99,9 +99,15 @@ bool automatic(const sslbm_launch &r) {
     return r.steps_per_pass == 0 && r.rows_per_wave == 0 && r.cols_per_lane == 0;
 }
 
+// The march shape asked for: the caller's, or the one the tuner found for a
+// context that it left on automatic shapes.
+const sslbm_launch &requested(const sslbm_ctx *c) {
+    return automatic(c->launch) ? c->tuned : c->launch;
+}
+
 // March shape of a pass: requested fields, automatic ones filled in.
 sslbm_launch resolve(const sslbm_ctx *c) {
-    sslbm_launch r = automatic(c->launch) ? c->tuned : c->launch;
+    sslbm_launch r = requested(c);
     if (r.steps_per_pass == 0)
         r.steps_per_pass = auto_depth(c);
     if (r.cols_per_lane == 0) {
@@ -156,8 +162,8 @@ sslbm::MarchShape shape_for(const sslbm_ctx *c, int k, const void *in, const voi
         (c->nx % 2 != 0 || (uintptr_t)in % pair != 0 || (uintptr_t)out % pair != 0 ||
          k > sslbm::march_max_depth(c->dtype, 2)))
         s.cols_per_lane = 1;
-    s.rows_per_wave =
-        c->launch.rows_per_wave > 0 ? c->launch.rows_per_wave : auto_rows(c, k, s.cols_per_lane);
+    const int rows = requested(c).rows_per_wave;
+    s.rows_per_wave = rows > 0 ? rows : auto_rows(c, k, s.cols_per_lane);
     return s;
 }
 

@@ -81,3 +81,22 @@ for (nx, ny), want in {ROUTES[dtype]!r}:
     # ensembles name their march kernel differently
     bad = [r for r in result if r[4] == "tile" and r[3] != ["tile"]]
     assert not bad, bad
+
+
+def test_marches_of_a_tuned_context_have_the_tuned_rows():
+    """After a tuning that tiles won, marches (single steps, recorded runs
+    every second step) run the shape that was timed, columns and rows."""
+    best, rows, auto = record('''
+h = context(900, 900)
+step = lambda: lib.sslbm_step(h, rho, scratch, None)
+passes(step)
+auto = rec.rec_arg(0, 4, 0)
+rec.rec_price(b"march", 6.0)
+rec.rec_price(b"tile", 0.1)
+best = Launch()
+assert lib.sslbm_tune(h, rho, scratch, None, ctypes.byref(best)) == 0
+assert {k[0] for k in passes(lambda: lib.sslbm_run(h, rho, scratch, 40, None))} == {"tile"}
+assert passes(step)[0] == ("march", 1, best.cols_per_lane)
+result = [best.as_dict(), rec.rec_arg(0, 4, 0), auto]
+''')
+    assert rows == best["rows_per_wave"] and rows != auto
