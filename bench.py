@@ -402,20 +402,18 @@ def run_surrogate(torch, inputs, Solver, train_steps):
     plain_ms = ev[0].elapsed_time(ev[1])
     plain_err = S.relative_l2(st, ref)
     roll = S.Rollout(sur, w.params, w.ny, w.nx, tiles=4, tile=64, target=1e-3, seed=0)
-    # its plain SSLBM steps are tuned the same way: a tuned solver may take
-    # register tiles, which set_launch cannot ask for
-    roll.solver.tune(rho0, scratch)
+    roll.solver.set_launch(**plain_launch)  # its plain SSLBM steps take the same shape
     roll.run(rho0, 100)  # warm-up (buffers, tables)
     final, rr = roll.run(rho0, T)
     roll_err = S.relative_l2(final, ref)
     # the surrogate alone: every jump accepted (still judged, for the error record)
     free = S.Rollout(sur, w.params, w.ny, w.nx, tiles=4, tile=64, threshold=1e30, seed=0,
                      backoff=False)
-    free.solver.tune(rho0, scratch)
+    free.solver.set_launch(**plain_launch)
     free_state, fr = free.run(rho0, T)
     free_err = S.relative_l2(free_state, ref)
     bare = S.Rollout(sur, w.params, w.ny, w.nx, threshold=float("inf"), seed=0, backoff=False)
-    bare.solver.tune(rho0, scratch)
+    bare.solver.set_launch(**plain_launch)
     _, br = bare.run(rho0, T)
     # time to T against the error target, for the trained 50-step network and
     # one trained the same way for 200-step jumps: plain SSLBM reaches every
@@ -431,7 +429,7 @@ def run_surrogate(torch, inputs, Solver, train_steps):
     for jump, model in nets:
         unjudged = S.Rollout(model, w.params, w.ny, w.nx, threshold=float("inf"), seed=0,
                              backoff=False)
-        unjudged.solver.tune(rho0, scratch)
+        unjudged.solver.set_launch(**plain_launch)
         unjudged.run(rho0, T)  # warm-up
         alone, ar = unjudged.run(rho0, T)
         net_pass_ms[jump] = ar.seconds * 1e3 / ar.jumps
@@ -440,7 +438,7 @@ def run_surrogate(torch, inputs, Solver, train_steps):
                       "jumps": ar.jumps, "speedup": round(plain_ms / (ar.seconds * 1e3), 4)})
         for target in (1e-3, 1e-2, 3e-2):
             rl = S.Rollout(model, w.params, w.ny, w.nx, tiles=4, tile=64, target=target, seed=0)
-            rl.solver.tune(rho0, scratch)
+            rl.solver.set_launch(**plain_launch)
             rl.run(rho0, 4 * jump)  # warm-up
             st_t, rt = rl.run(rho0, T)
             e = S.relative_l2(st_t, ref)

@@ -167,6 +167,18 @@ sslbm_status sslbm_set_launch(sslbm_ctx *c, const sslbm_launch *shape);
 sslbm_status sslbm_get_launch(const sslbm_ctx *c, sslbm_launch *shape);
 
 /*
+ * Passes of tiles asked for, as sslbm_tune leaves a context whose tuning they
+ * won: sslbm_run takes them without an estimate of its own, and passes that
+ * are marches all the same (single steps) have the shape `march` (every field
+ * given, within the register limit). SSLBM_E_UNSUPPORTED on grids too large
+ * for tiles. sslbm_set_launch and sslbm_set_blocking end it.
+ *   sslbm_get_tiles: 1 if the context is so set, by the call or by sslbm_tune.
+ *       With sslbm_get_launch it tells a tuned choice to another context.
+ */
+sslbm_status sslbm_set_tiles(sslbm_ctx *c, const sslbm_launch *march);
+int sslbm_get_tiles(const sslbm_ctx *c);
+
+/*
  * Autotuner: times candidate launch shapes of sslbm_run on the caller's
  * state and keeps the fastest (it becomes the context's shape; *best, if not
  * NULL, receives it). Candidates: one and (for an even row length and

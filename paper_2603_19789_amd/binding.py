@@ -97,6 +97,8 @@ def library() -> ctypes.CDLL:
             "sslbm_get_blocking": [vp],
             "sslbm_set_launch": [vp, ctypes.POINTER(Launch)],
             "sslbm_get_launch": [vp, ctypes.POINTER(Launch)],
+            "sslbm_set_tiles": [vp, ctypes.POINTER(Launch)],
+            "sslbm_get_tiles": [vp],
             "sslbm_tune": [vp, vp, vp, vp, ctypes.POINTER(Launch)],
             "sslbm_step": [vp, vp, vp, vp],
             "sslbm_run": [vp, vp, vp, ll, vp],
@@ -295,22 +297,27 @@ class Solver(_Context):
     def blocking(self) -> int:
         return self.lib.sslbm_get_blocking(self.handle)
 
-    def set_launch(self, steps_per_pass=0, rows_per_wave=0, cols_per_lane=0):
-        """Pass shape (0 = automatic); changes speed, never results."""
+    def set_launch(self, steps_per_pass=0, rows_per_wave=0, cols_per_lane=0, tiles=False):
+        """Pass shape (0 = automatic); changes speed, never results. With
+        `tiles`, runs take passes of register tiles and the shape is that of
+        the other passes: `set_launch(**other.tune(...))` passes a tuned choice
+        on, whichever kind won."""
         shape = Launch(int(steps_per_pass), int(rows_per_wave), int(cols_per_lane))
-        self._check(self.lib.sslbm_set_launch(self.handle, ctypes.byref(shape)),
-                    "sslbm_set_launch")
+        name = "sslbm_set_tiles" if tiles else "sslbm_set_launch"
+        self._check(getattr(self.lib, name)(self.handle, ctypes.byref(shape)), name)
 
     def launch(self) -> dict:
-        """The pass shape sslbm_run uses, automatic fields resolved."""
+        """The pass shape sslbm_run uses, automatic fields resolved; "tiles":
+        True besides where tiles were found faster (`tune`) or asked for."""
         shape = Launch()
         self._check(self.lib.sslbm_get_launch(self.handle, ctypes.byref(shape)),
                     "sslbm_get_launch")
-        return shape.as_dict()
+        tiles = {"tiles": True} if self.lib.sslbm_get_tiles(self.handle) else {}
+        return {**shape.as_dict(), **tiles}
 
     def tune(self, rho, scratch=None, stream=None) -> dict:
         """Time candidate pass shapes on `rho` (only read; `scratch` is
-        overwritten) and keep the fastest; returns it."""
+        overwritten) and keep the fastest; returns it, as `launch` does."""
         if scratch is None:
             scratch = self.empty(*self.shape)
         a = self._tensor(rho, self.shape, "rho")
@@ -318,7 +325,7 @@ class Solver(_Context):
         best = Launch()
         self._check(self.lib.sslbm_tune(self.handle, a, b, _stream(stream), ctypes.byref(best)),
                     "sslbm_tune")
-        return best.as_dict()
+        return self.launch()
 
     def step(self, rho_in, rho_out=None, stream=None):
         """One time step rho_in -> rho_out (allocated when not given)."""

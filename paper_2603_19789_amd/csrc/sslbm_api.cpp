@@ -368,10 +368,8 @@ sslbm_status sslbm_set_params(sslbm_ctx *c, const sslbm_params *p) {
     return SSLBM_OK;
 }
 
-sslbm_status sslbm_set_launch(sslbm_ctx *c, const sslbm_launch *shape) {
-    if (!c || !shape)
-        return SSLBM_E_ARG;
-    const sslbm_launch &r = *shape;
+// Checks of a requested march shape.
+static sslbm_status launch_status(const sslbm_ctx *c, const sslbm_launch &r) {
     if (r.steps_per_pass < 0 || r.steps_per_pass > SSLBM_MAX_BLOCKING || r.rows_per_wave < 0 ||
         r.rows_per_wave > 65536 || r.cols_per_lane < 0 || r.cols_per_lane > 2)
         return SSLBM_E_ARG;
@@ -382,9 +380,37 @@ sslbm_status sslbm_set_launch(sslbm_ctx *c, const sslbm_launch *shape) {
     const sslbm_launch full = resolve(&probe);
     if (full.steps_per_pass > sslbm::march_max_depth(c->dtype, full.cols_per_lane))
         return SSLBM_E_UNSUPPORTED;
-    c->launch = r;
+    return SSLBM_OK;
+}
+
+sslbm_status sslbm_set_launch(sslbm_ctx *c, const sslbm_launch *shape) {
+    if (!c || !shape)
+        return SSLBM_E_ARG;
+    const sslbm_status st = launch_status(c, *shape);
+    if (st != SSLBM_OK)
+        return st;
+    c->launch = *shape;
     c->tuned = sslbm_launch{};
     return SSLBM_OK;
+}
+
+sslbm_status sslbm_set_tiles(sslbm_ctx *c, const sslbm_launch *march) {
+    if (!c || !march || march->steps_per_pass < 1 || march->rows_per_wave < 1 ||
+        march->cols_per_lane < 1)
+        return SSLBM_E_ARG;
+    const sslbm_status st = launch_status(c, *march);
+    if (st != SSLBM_OK)
+        return st;
+    const sslbm::GridSize size{c->nx, c->ny, 1};
+    if (sslbm::tile_plan(c->dtype, &size, 1, 1000).rows == 0)
+        return SSLBM_E_UNSUPPORTED;
+    c->launch = sslbm_launch{};
+    c->tuned = *march;
+    return SSLBM_OK;
+}
+
+int sslbm_get_tiles(const sslbm_ctx *c) {
+    return c && automatic(c->launch) && c->tuned.steps_per_pass > 0 ? 1 : 0;
 }
 
 sslbm_status sslbm_get_launch(const sslbm_ctx *c, sslbm_launch *shape) {

@@ -100,3 +100,42 @@ assert passes(step)[0] == ("march", 1, best.cols_per_lane)
 result = [best.as_dict(), rec.rec_arg(0, 4, 0), auto]
 ''')
     assert rows == best["rows_per_wave"] and rows != auto
+
+
+def test_a_tuned_choice_of_tiles_can_be_passed_on():
+    """The shape that a tuning reports, set on another context, gives that
+    context the same passes, through the C ABI and the Python class."""
+    a, b, march, codes, py, py_march = record('''
+run = lambda c: passes(lambda: lib.sslbm_run(c, rho, scratch, 40, None))
+h, other = context(1090, 1090), context(1090, 1090)
+rec.rec_price(b"march", 6.0)
+rec.rec_price(b"tile", 0.1)
+best = Launch()
+assert lib.sslbm_tune(h, rho, scratch, None, ctypes.byref(best)) == 0
+assert lib.sslbm_get_tiles(h) == 1 and lib.sslbm_get_tiles(other) == 0
+assert lib.sslbm_set_tiles(other, ctypes.byref(best)) == 0 and lib.sslbm_get_tiles(other) == 1
+a, b = run(h), run(other)
+assert lib.sslbm_set_launch(other, ctypes.byref(best)) == 0 and lib.sslbm_get_tiles(other) == 0
+march = run(other)
+large = context(2000, 2000)
+codes = [lib.sslbm_set_tiles(large, ctypes.byref(best)), lib.sslbm_set_tiles(other, None),
+         lib.sslbm_set_tiles(other, ctypes.byref(Launch(4, 8, 0))),
+         lib.sslbm_set_tiles(other, ctypes.byref(Launch(8, 8, 2))),
+         lib.sslbm_set_tiles(other, ctypes.byref(Launch(99, 8, 1)))]
+assert lib.sslbm_get_tiles(other) == 0
+from paper_2603_19789_amd import Solver
+s = Solver(300, 200, params(), dtype="f32")
+assert "tiles" not in s.launch()
+s.set_launch(4, 8, 1, tiles=True)
+t = Solver(300, 200, params(), dtype="f32")
+t.set_launch(**s.launch())
+py = [s.launch(), t.launch(), t.plan(1000)["longest"]]
+t.set_launch(4, 8, 1)
+py_march = [t.launch(), t.plan(1000)["longest"]]
+result = [a, b, march, codes, py, py_march]
+''')
+    assert a == b and {k[0] for k in a} == {"tile"} and {k[0] for k in march} == {"march"}
+    assert codes == [-3, -1, -1, -3, -1]
+    want = {"steps_per_pass": 4, "rows_per_wave": 8, "cols_per_lane": 1}
+    assert py[0] == py[1] == {**want, "tiles": True} and py[2] > 4
+    assert py_march == [want, 4]
