@@ -45,12 +45,16 @@ sslbm_status hip_status(sslbm_ctx *c, hipError_t e) {
 // Steps per pass and columns per lane when the caller has not chosen: the
 // fastest shapes measured on MI355X for large grids (the pass turns from
 // HBM-bound to ALU-bound around there). FP64 with a diffusing D takes one step
-// less: its five-step kernel spills (172 B of scratch per lane; 1024^2: 6.8 us
-// a step against 5.9, 640^2: 4.15 against 3.23).
+// less while the two states fit the 256 MB last-level cache: its five-step
+// kernel spills (172 B of scratch per lane; 60 steps of 1024^2 338 against 384
+// us, of 1700^2 724 against 789). Beyond it HBM decides and five win again
+// (1800^2 923 against 980 us, 2048^2 1160 against 1301, 4096^2 3994 against
+// 4874).
 int auto_depth(const sslbm_ctx *c) {
+    constexpr size_t CACHED_CELLS = 3000000;  // two states of 40 bytes a cell
     if (c->dtype == SSLBM_F32)
         return 6;
-    return c->coef.diffuse_d ? 4 : 5;
+    return c->coef.diffuse_d && plane_elems(c) <= CACHED_CELLS ? 4 : 5;
 }
 int auto_cols(const sslbm_ctx *c) { return c->dtype == SSLBM_F32 ? 2 : 1; }
 

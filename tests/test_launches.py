@@ -139,3 +139,16 @@ result = [a, b, march, codes, py, py_march]
     want = {"steps_per_pass": 4, "rows_per_wave": 8, "cols_per_lane": 1}
     assert py[0] == py[1] == {**want, "tiles": True} and py[2] > 4
     assert py_march == [want, 4]
+
+
+def test_depth_with_a_diffusing_dead_compartment():
+    """FP64 runs with a diffusing D: four steps a pass while two states fit the
+    last-level cache, five beyond; without it, and in FP32, any size the same."""
+    result = record('''
+result = []
+for n, d in ((1500, 3e-3), (1700, 3e-3), (1800, 3e-3), (2048, 3e-3), (4096, 3e-3), (1500, 0.0),
+             (4096, 0.0)):
+    result.append([passes(lambda: lib.sslbm_run(context(n, n, t, d), rho, scratch, 60, None))[0][1]
+                   for t in ("f64", "f32")])
+''')
+    assert result == [[4, 6], [4, 6], [5, 6], [5, 6], [5, 6], [5, 6], [5, 6]]
