@@ -201,14 +201,17 @@ hipError_t launch_shape(const void *in, void *out, const GridDesc &g, const Coef
 // Tile height: the lowest tile that still gives every CU no more than one
 // (4 output rows; 200^2 FP64 8.8 us a step, 10.2 with 8 rows, 18.2 with 32),
 // or two (8 rows; 400^2 FP64 19.1 us, 27.1 with 4 rows, 19.5 with 32); larger
-// grids the tallest, which wastes least (2048^2 FP64: 245 us, 370 with 8).
+// grids the tallest, which wastes least (2048^2 FP64: 245 us, 370 with 8). Grids
+// of up to 4 and 16 rows take the lowest tile that holds them or half of them: a
+// tile costs what its rows with the halo do (65536 columns, FP32 and FP64: 21 and
+// 36 us a step for 4 output rows, 25 and 44 for 8, 61 and 95 for 32).
 template <typename T, bool DD>
 hipError_t launch_step(const void *in, void *out, const GridDesc &g, const Coef<T> &k, int cus,
                        hipStream_t st) {
     const long long strips = (g.nx + FD4_COLS - 1) / FD4_COLS;
-    if (strips * ((g.ny + 3) / 4) <= cus)
+    if (g.ny <= 4 || strips * ((g.ny + 3) / 4) <= cus)
         return launch_shape<T, 2, 10, DD>(in, out, g, k, st);
-    if (strips * ((g.ny + 7) / 8) <= 2 * cus)
+    if (g.ny <= 16 || strips * ((g.ny + 7) / 8) <= 2 * cus)
         return launch_shape<T, 3, 8, DD>(in, out, g, k, st);
     return launch_shape<T, 6, 8, DD>(in, out, g, k, st);
 }

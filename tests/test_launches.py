@@ -152,3 +152,23 @@ for n, d in ((1500, 3e-3), (1700, 3e-3), (1800, 3e-3), (2048, 3e-3), (4096, 3e-3
                    for t in ("f64", "f32")])
 ''')
     assert result == [[4, 6], [4, 6], [5, 6], [5, 6], [5, 6], [5, 6], [5, 6]]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_finite_difference_tiles_fit_low_grids(dtype):
+    """The finite-difference step takes low tiles on grids of a few rows,
+    however wide they are (columns, rows -> output rows of a tile)."""
+    cases = [(65536, 1, 4), (262144, 4, 4), (65536, 5, 8), (65536, 16, 8), (65536, 17, 32),
+             (200, 200, 4), (400, 400, 8), (2048, 2048, 32)]
+    result = record(f'''
+result = []
+for nx, ny, _ in {cases!r}:
+    h = context(nx, ny, {dtype!r})
+    size = lib.sslbm_fd4_workspace_bytes(h)
+    kinds = passes(lambda: lib.sslbm_fd4_run(h, rho, scratch, size, 3, None))
+    (kernel, args, grid, *_), *rest = launched()
+    rows = int(args[1]) * int(args[2]) - 16
+    assert len(rest) == 2 and grid == -(-nx // 48) * -(-ny // rows)
+    result.append([nx, ny, rows])
+''')
+    assert result == [list(c) for c in cases]
