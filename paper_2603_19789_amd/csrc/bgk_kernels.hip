@@ -167,11 +167,13 @@ constexpr int BGK_MAX_DEPTH = sizeof(T) == 4 ? 7 : 3;
 // few rows each to pay for its halo: from 384^2 on it is ahead (FP32 5.5 us a
 // step against 5.8, FP64 7.9 against 9.7), at 256^2 behind (FP32 5.6 against
 // 4.0, FP64 7.5 against 5.9), and a strip narrower than half a wavefront
-// would compute mostly halo. FP32 takes seven steps on grids large enough
-// that HBM decides (1536^2: 22.0 us a step against 23.5 at five) and five
-// below, where the halo does (1024^2: 12.9 against 13.4).
+// would compute mostly halo, as a single row would (150000 x 1, 42 steps: FP32
+// 348 us against 231 of single steps, FP64 486 against 379; two rows are even).
+// FP32 takes seven steps on grids large enough that HBM decides (1536^2: 22.0 us
+// a step against 23.5 at five) and five below, where the halo does (1024^2: 12.9
+// against 13.4).
 int bgk_depth(int dtype, const GridDesc &g) {
-    if (g.plane < 140000 || g.nx < 32)
+    if (g.plane < 140000 || g.nx < 32 || g.ny < 2)
         return 1;
     if (dtype == SSLBM_F64)
         return BGK_MAX_DEPTH<double>;

@@ -69,6 +69,10 @@ def passes(call):
             out.append(("march", int(args[1]), int(args[3])))
         elif kernel == "sslbm_march_mid_kernel":
             out.append(("mid", int(args[1]), int(args[3])))
+        elif kernel == "bgk_march_kernel":
+            out.append(("bgk", int(args[1]), None))
+        elif kernel == "bgk_step_kernel":
+            out.append(("bgk", 1, None))
         elif "tile_kernel" in kernel:
             out.append(("tile", None, int(args[1])))
         else:

@@ -172,3 +172,20 @@ for nx, ny, _ in {cases!r}:
     result.append([nx, ny, rows])
 ''')
     assert result == [list(c) for c in cases]
+
+
+def test_bgk_depth_over_forms_of_grids():
+    """Passes of several steps need rows and columns that are not mostly halo."""
+    cases = [(150000, 1, 1, 1), (1000000, 1, 1, 1), (300000, 2, 5, 3), (31, 60000, 1, 1),
+             (32, 60000, 7, 3), (256, 256, 1, 1), (1024, 1024, 5, 3), (2048, 2048, 7, 3)]
+    result = record(f'''
+result = []
+for nx, ny, *_ in {cases!r}:
+    row = [nx, ny]
+    for dtype in ("f32", "f64"):
+        h, d, ds = context(nx, ny, dtype), ctypes.c_void_p(4 << 40), ctypes.c_void_p(5 << 40)
+        kinds = passes(lambda: lib.bgk_run(h, rho, d, scratch, ds, 210, None))
+        row.append(max(k[1] for k in kinds))
+    result.append(row)
+''')
+    assert result == [list(c) for c in cases]
