@@ -169,13 +169,53 @@ int auto_cols(const sslbm_ensemble *e, int K) {
     return covered[1] <= covered[0] + covered[0] / 32 ? 2 : 1;
 }
 
+// The fewest rows per wavefront, at least `least`, for which the tiles of grids
+// of some sizes number at most `tiles` (the highest grid's rows if none are).
+int rows_for(const std::vector<sslbm::GridSize> &sizes, int w, long long tiles, int least,
+             int most) {
+    int lo = least, hi = std::max(least, most);
+    while (lo < hi) {
+        const int mid = lo + (hi - lo) / 2;
+        if (count_tiles(sizes, w, mid) <= tiles)
+            hi = mid;
+        else
+            lo = mid + 1;
+    }
+    return lo;
+}
+
+// Automatic rows per wavefront of passes of K steps over grids of some sizes:
+// the fewest for which all their tiles are resident at once, the same rows for
+// every class of a pass (it lasts as long as its longest march; with rows by
+// each class's share of the GPU the smallest class had the tallest ones, and 96
+// grids of 64^2 to 512^2 took 390 GLUPS). Where that gives chunks of fewer than
+// 16 rows, a wavefront less per SIMD on taller ones may be faster, as estimated
+// (FP32, 60 steps: 8 grids of 512^2 330 us at 12 rows and two wavefronts a SIMD,
+// 392 at 16; 6 of them 325 at 12 rows, 290 at 16 and one wavefront).
+int auto_rows(const sslbm_ensemble *e, const std::vector<sslbm::GridSize> &sizes, int K, int V) {
+    long long resident = sslbm::march_resident_waves(e->dtype, K, V, e->diffuse_d);
+    if (resident <= 0)
+        resident = 2 * 4 * 256;
+    const int w = sslbm::strip_width(K, V), least = 2 * K, most = e->march_max_side;
+    int best = rows_for(sizes, w, resident, least, most);
+    if (best >= 16)
+        return best;
+    double best_us = 0.0;
+    const int simds = 4 * sslbm::compute_units();
+    for (long long share = resident / simds; share >= 1; --share) {
+        const int rows = rows_for(sizes, w, share * simds, least, most);
+        const double us = sslbm::march_us(e->dtype, K, V, rows, count_tiles(sizes, w, rows));
+        if (best_us == 0.0 || us < best_us) {
+            best_us = us;
+            best = rows;
+        }
+    }
+    return best;
+}
+
 // Pass shape of march class c: requested fields, automatic ones filled in.
-// Automatic: the single-grid depth; columns as above; rows per wavefront the
-// fewest, at least 16, for which the tiles of every march class (of class c
-// alone where it runs alone) are resident at once. The same rows for all
-// classes: a pass lasts as long as its longest march, and with rows by each
-// class's share of the GPU the smallest class had the tallest ones (96 grids
-// of 64^2 to 512^2: 390 GLUPS against 474).
+// Automatic: six steps in FP32, five in FP64; columns and rows as above, over
+// every march class (over class c alone where it runs alone).
 sslbm_launch resolve(const sslbm_ensemble *e, int c, bool pairs_ok = true, bool alone = false) {
     const EnsClass &cl = e->classes[c];
     sslbm_launch r = cl.launch;
@@ -189,23 +229,9 @@ sslbm_launch resolve(const sslbm_ensemble *e, int c, bool pairs_ok = true, bool 
                     r.cols_per_lane, usable_cols(e, i, r.cols_per_lane, r.steps_per_pass, pairs_ok));
     }
     r.cols_per_lane = usable_cols(e, c, r.cols_per_lane, r.steps_per_pass, pairs_ok);
-    if (r.rows_per_wave == 0) {
-        long long resident =
-            sslbm::march_resident_waves(e->dtype, r.steps_per_pass, r.cols_per_lane, e->diffuse_d);
-        if (resident <= 0)
-            resident = 2 * 4 * 256;
-        const std::vector<sslbm::GridSize> &sizes = alone ? cl.sizes : e->march_sizes;
-        const int w = sslbm::strip_width(r.steps_per_pass, r.cols_per_lane);
-        int lo = std::max(16, 2 * r.steps_per_pass), hi = std::max(lo, e->march_max_side);
-        while (lo < hi) {  // smallest H with count_tiles(H) <= resident
-            const int mid = lo + (hi - lo) / 2;
-            if (count_tiles(sizes, w, mid) <= resident)
-                hi = mid;
-            else
-                lo = mid + 1;
-        }
-        r.rows_per_wave = lo;
-    }
+    if (r.rows_per_wave == 0)
+        r.rows_per_wave =
+            auto_rows(e, alone ? cl.sizes : e->march_sizes, r.steps_per_pass, r.cols_per_lane);
     return r;
 }
 

@@ -50,17 +50,19 @@ static double pass_us(int dtype, int R, int K, int rows, long long tiles, int cu
 }
 
 // From a fit to 640 measured passes (grids and ensembles of up to 4 million
-// cells, 1 to 10 wavefronts a SIMD; FP32 5% rms with one column a lane and 6%
-// with two, FP64 9%): a wavefront computes H rows of every level and half of
-// 2K more while they fill, and the wavefronts of a SIMD share its issue slots.
+// cells, 1 to 10 wavefronts a SIMD; FP32 5% rms with one column a lane and 4%
+// with two, FP64 7%): a wavefront computes H rows of every level and half of
+// 2K more while they fill; the wavefronts of a SIMD share its issue slots, and
+// the third and later ones start when others end, or crowd the caches.
 double march_us(int dtype, int K, int cols_per_lane, int H, long long waves) {
     const int simds = 4 * compute_units();
     const double rows = (double)H * K + (double)K * K;
     const double share = (double)((waves + simds - 1) / simds);
+    const double more = share > 2.0 ? share - 2.0 : 0.0;
     if (dtype == SSLBM_F64)
-        return 3.29 + rows * (0.0123 + 0.1335 * share);
-    return cols_per_lane == 2 ? 4.61 + rows * (0.0697 + 0.1032 * share)
-                              : 2.82 + rows * (0.0574 + 0.0547 * share);
+        return 1.98 + rows * (0.0889 + 0.0916 * share + 0.0570 * more);
+    return cols_per_lane == 2 ? 4.38 + rows * (0.1135 + 0.0753 * share + 0.0516 * more)
+                              : 2.35 + rows * (0.0768 + 0.0452 * share + 0.0116 * more);
 }
 
 TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps, bool fewest) {

@@ -189,3 +189,19 @@ for nx, ny, *_ in {cases!r}:
     result.append(row)
 ''')
     assert result == [list(c) for c in cases]
+
+
+def test_rows_of_small_ensembles():
+    """Automatic rows per wavefront of ensembles just too large for tiles: the
+    faster of one and two wavefronts a SIMD, not a fixed least height."""
+    cases = [(8, 512, 12), (6, 512, 16), (3, 1024, 14), (40, 512, 52)]
+    result = record(f'''
+result = []
+for n, side, _ in {cases!r}:
+    e = ensemble([(side, side)] * n)
+    assert passes(lambda: lib.sslbm_ensemble_run(e, rho, scratch, 12, 0, None))
+    info = binding.EnsembleClass()
+    assert lib.sslbm_ensemble_class_info(e, 0, ctypes.byref(info)) == 0
+    result.append([n, side, info.as_dict()["launch"]["rows_per_wave"]])
+''')
+    assert result == [list(c) for c in cases]
