@@ -31,6 +31,7 @@
 #include <cstdint>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <new>
 #include <tuple>
 #include <vector>
@@ -72,6 +73,16 @@ struct EnsClass {
     hipEvent_t done = nullptr;
 };
 
+// One chain of passes over some march classes: register tiles (tiles.rows > 0),
+// or marches of K steps with V columns per lane and H rows of each class.
+struct Chain {
+    std::vector<int> classes;
+    sslbm::TilePlan tiles;
+    int K = 0, V = 0;
+    std::vector<int> H;
+    int depth() const { return tiles.rows ? tiles.depth : K; }
+};
+
 }  // namespace
 
 struct sslbm_ensemble {
@@ -97,6 +108,12 @@ struct sslbm_ensemble {
     hipStream_t stream = nullptr;  // graph and tuning stream
     hipEvent_t ev_in = nullptr, ev_out = nullptr, ev_fork = nullptr;
     std::map<GraphKey, hipGraphExec_t> graphs;
+    // the chains of the last run, which the next one most often repeats
+    std::mutex planned_lock;
+    long long planned_steps = -1;
+    bool planned_pairs = false;
+    std::vector<Chain> planned;
+    int tiles_pay[2] = {-1, -1};  // by pair alignment: tiles are faster (-1: not yet known)
 };
 
 namespace {
@@ -254,7 +271,13 @@ void count_size(std::vector<sslbm::GridSize> *sizes,
     ++(*sizes)[it.first->second].count;
 }
 
-void drop_graphs(sslbm_ensemble *e) {
+// Graphs and plans made with shapes that changed.
+void drop_plans(sslbm_ensemble *e) {
+    {
+        std::lock_guard<std::mutex> guard(e->planned_lock);
+        e->planned_steps = -1;
+        e->tiles_pay[0] = e->tiles_pay[1] = -1;
+    }
     for (auto &g : e->graphs)
         (void)hipGraphExecDestroy(g.second);
     e->graphs.clear();
@@ -310,16 +333,6 @@ sslbm_status ensure_device_tables(sslbm_ensemble *e) {
     return SSLBM_OK;
 }
 
-// One chain of passes over some march classes: register tiles (tiles.rows > 0),
-// or marches of K steps with V columns per lane and H rows of each class.
-struct Chain {
-    std::vector<int> classes;
-    sslbm::TilePlan tiles;
-    int K = 0, V = 0;
-    std::vector<int> H;
-    int depth() const { return tiles.rows ? tiles.depth : K; }
-};
-
 // Estimated time of a step by a chain's marches.
 double march_step_us(const sslbm_ensemble *e, const Chain &ch) {
     const int w = sslbm::strip_width(ch.K, ch.V);
@@ -333,28 +346,37 @@ double march_step_us(const sslbm_ensemble *e, const Chain &ch) {
 }
 
 // Tiles of a chain whose shapes are all automatic: as for a single grid, none
-// where its grids are too large for them or the march is estimated to be faster.
+// where its grids are too large for them or the march is estimated to be faster
+// (an answer for runs of every length, kept in *pay, -1 before).
 sslbm::TilePlan chain_tiles(const sslbm_ensemble *e, const std::vector<sslbm::GridSize> &sizes,
-                            const Chain &ch, long long nsteps) {
+                            const Chain &ch, long long nsteps, int *pay) {
     const int n = (int)sizes.size();
+    if (*pay == 0)
+        return sslbm::TilePlan();
     const sslbm::TilePlan tiles = sslbm::tile_plan(e->dtype, sizes.data(), n, nsteps);
-    if (tiles.rows == 0 || tiles.few || e->tiles_tuned ||
-        sslbm::tiles_pay(e->dtype, sizes.data(), n, march_step_us(e, ch)))
+    if (tiles.rows == 0 || tiles.few || e->tiles_tuned)
         return tiles;
-    return sslbm::TilePlan();
+    if (*pay < 0)
+        *pay = sslbm::tiles_pay(e->dtype, sizes.data(), n, march_step_us(e, ch)) ? 1 : 0;
+    return *pay ? tiles : sslbm::TilePlan();
 }
 
 // The march chains of a run of nsteps.
-std::vector<Chain> march_chains(const sslbm_ensemble *e, long long nsteps, bool pairs_ok) {
+std::vector<Chain> march_chains(const sslbm_ensemble *e, long long nsteps, bool pairs_ok,
+                                int *pay) {
     std::vector<Chain> out;
     bool automatic = true, alike = true;
+    sslbm_launch joint{};  // the shape of every class with automatic ones
     for (int c = 0; c < (int)e->classes.size(); ++c) {
         const EnsClass &cl = e->classes[c];
         if (cl.on_chip)
             continue;
-        automatic = automatic && cl.launch.steps_per_pass == 0 && cl.launch.rows_per_wave == 0 &&
-                    cl.launch.cols_per_lane == 0;
-        const sslbm_launch r = resolve(e, c, pairs_ok);
+        const bool own = cl.launch.steps_per_pass == 0 && cl.launch.rows_per_wave == 0 &&
+                         cl.launch.cols_per_lane == 0;
+        automatic = automatic && own;
+        const sslbm_launch r = own && joint.steps_per_pass ? joint : resolve(e, c, pairs_ok);
+        if (own)
+            joint = r;
         Chain ch;
         ch.classes = {c};
         ch.K = r.steps_per_pass;
@@ -373,15 +395,29 @@ std::vector<Chain> march_chains(const sslbm_ensemble *e, long long nsteps, bool 
         }
         out.resize(1);
         if (automatic)
-            out[0].tiles = chain_tiles(e, e->march_sizes, out[0], nsteps);
+            out[0].tiles = chain_tiles(e, e->march_sizes, out[0], nsteps, pay);
     }
     return out;
+}
+
+// The same, kept from the last run: working out the shapes of many sizes takes
+// longer than a short run of a small ensemble (20 grids of 65^2 to 160^2, 6
+// steps in FP32: 14 us with the plan kept, 23 planned anew each time).
+std::vector<Chain> run_chains(sslbm_ensemble *e, long long nsteps, bool pairs_ok) {
+    std::lock_guard<std::mutex> guard(e->planned_lock);
+    if (e->planned_steps != nsteps || e->planned_pairs != pairs_ok) {
+        e->planned = march_chains(e, nsteps, pairs_ok, &e->tiles_pay[pairs_ok]);
+        e->planned_steps = nsteps;
+        e->planned_pairs = pairs_ok;
+    }
+    return e->planned;
 }
 
 // The chain of one march class run on its own.
 Chain class_chain(const sslbm_ensemble *e, int c, long long nsteps, bool pairs_ok) {
     const EnsClass &cl = e->classes[c];
     const sslbm_launch r = resolve(e, c, pairs_ok, true);
+    int pay = -1;
     Chain ch;
     ch.classes = {c};
     ch.K = r.steps_per_pass;
@@ -389,7 +425,7 @@ Chain class_chain(const sslbm_ensemble *e, int c, long long nsteps, bool pairs_o
     ch.H = {r.rows_per_wave};
     if (cl.launch.steps_per_pass == 0 && cl.launch.rows_per_wave == 0 &&
         cl.launch.cols_per_lane == 0)
-        ch.tiles = chain_tiles(e, cl.sizes, ch, nsteps);
+        ch.tiles = chain_tiles(e, cl.sizes, ch, nsteps, &pay);
     return ch;
 }
 
@@ -570,7 +606,8 @@ sslbm_status check_shape(const sslbm_ensemble *e, const sslbm_launch &r) {
 double joint_rate(sslbm_ensemble *e, const void *rho, void *scratch, bool pairs_ok,
                   hipEvent_t t0, hipEvent_t t1, sslbm_status *status) {
     sslbm_status st = SSLBM_OK;
-    const std::vector<Chain> chains = march_chains(e, 1000, pairs_ok);
+    int pay = -1;
+    const std::vector<Chain> chains = march_chains(e, 1000, pairs_ok, &pay);
     double work = 0.0;  // cell-updates of one round
     for (const Chain &ch : chains)
         for (int c : ch.classes)
@@ -830,7 +867,7 @@ sslbm_status sslbm_ensemble_set_class_launch(sslbm_ensemble *e, int cls,
         return SSLBM_E_UNSUPPORTED;
     e->classes[cls].launch = *shape;
     e->tiles_tuned = false;
-    drop_graphs(e);
+    drop_plans(e);
     return SSLBM_OK;
 }
 
@@ -844,7 +881,7 @@ sslbm_status sslbm_ensemble_set_launch(sslbm_ensemble *e, const sslbm_launch *sh
         if (!cl.on_chip)
             cl.launch = *shape;
     e->tiles_tuned = false;
-    drop_graphs(e);
+    drop_plans(e);
     return SSLBM_OK;
 }
 
@@ -901,7 +938,7 @@ sslbm_status sslbm_ensemble_run(sslbm_ensemble *e, void *rho, void *scratch, lon
     st = ensure_device_tables(e);
     if (st != SSLBM_OK)
         return st;
-    const std::vector<Chain> chains = march_chains(e, nsteps, pairs_ok);
+    const std::vector<Chain> chains = run_chains(e, nsteps, pairs_ok);
     st = prepare_chains(e, chains, nsteps, pairs_ok);
     if (st != SSLBM_OK)
         return st;
@@ -984,7 +1021,7 @@ sslbm_status sslbm_ensemble_tune(sslbm_ensemble *e, const void *rho, void *scrat
         e->tiles_tuned = saved_tiles;
         return st;
     }
-    drop_graphs(e);
+    drop_plans(e);
     if (best)
         sslbm_ensemble_get_launch(e, best);
     return SSLBM_OK;
@@ -995,7 +1032,7 @@ int sslbm_ensemble_last_hip_error(const sslbm_ensemble *e) { return e ? e->last_
 void sslbm_ensemble_destroy(sslbm_ensemble *e) {
     if (!e)
         return;
-    drop_graphs(e);
+    drop_plans(e);
     for (auto &t : e->tiles)
         (void)hipFree(t.second.dev);
     if (e->insts)

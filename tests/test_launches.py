@@ -205,3 +205,23 @@ for n, side, _ in {cases!r}:
     result.append([n, side, info.as_dict()["launch"]["rows_per_wave"]])
 ''')
     assert result == [list(c) for c in cases]
+
+
+def test_an_ensemble_run_is_planned_once():
+    """A run that repeats the last one's steps makes no new plan; one with other
+    steps, or after a change of shapes, does."""
+    first, again, changed, shapes = record('''
+e = ensemble([(65 + 7 * i, 90 + 3 * i) for i in range(20)] + [(300, 200)])
+run = lambda n: passes(lambda: lib.sslbm_ensemble_run(e, rho, scratch, n, 0, None))
+a = run(6); first = rec.rec_queries()
+b = run(6); again = rec.rec_queries()
+assert a == b and {k[0] for k in a} == {"tile"}
+run(60); changed = rec.rec_queries()
+assert lib.sslbm_ensemble_set_launch(e, ctypes.byref(Launch(3, 16, 1))) == 0
+c = run(60)
+assert lib.sslbm_ensemble_set_launch(e, ctypes.byref(Launch(0, 0, 0))) == 0
+d = run(60)
+result = [first, again, changed, [len(c), sorted({k[0] for k in c}), sorted({k[0] for k in d})]]
+''')
+    assert again == 1 < min(first, changed)  # one query: the device the ensemble is on
+    assert shapes == [20, ["ensemble_march_kernel"], ["tile"]]
