@@ -186,11 +186,7 @@ int bgk_depth(int dtype, const GridDesc &g) {
 // grids give every SIMD its two wavefronts (2048^2 at seven steps: 42 rows
 // 33 us, 64 rows 43).
 static int bgk_rows_per_wave(const GridDesc &g, int strips) {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 1)
-        cus = 256;
+    const int cus = compute_units();
     auto rows = [&](int waves) {
         const int chunks = waves / strips > 1 ? waves / strips : 1;
         return (g.ny + chunks - 1) / chunks;

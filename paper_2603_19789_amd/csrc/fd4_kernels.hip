@@ -227,11 +227,7 @@ hipError_t launch_t(void *rho, void *work, const GridDesc &g, const StepCoef &s,
     k.kI = (T)s.kI;
     k.kR = (T)s.kR;
     k.kD = (T)s.kD;
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus < 1)
-        cus = 256;
+    const int cus = compute_units();
     T *u = static_cast<T *>(rho), *w0 = static_cast<T *>(work), *w1 = w0 + 5 * g.plane;
     auto step = [&](const T *in, T *out) {
         return s.diffuse_d ? launch_step<T, true>(in, out, g, k, cus, st)

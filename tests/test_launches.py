@@ -225,3 +225,27 @@ result = [first, again, changed, [len(c), sorted({k[0] for k in c}), sorted({k[0
 ''')
     assert again == 1 < min(first, changed)  # one query: the device the ensemble is on
     assert shapes == [20, ["ensemble_march_kernel"], ["tile"]]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_launches_without_an_answer_from_the_device(dtype):
+    """Where the device cannot be asked for its compute units the launchers
+    take an MI355X's, and the query's error is not the launches' one."""
+    result = record(f'''
+calls = []
+for there in (1, 0):
+    h, d, ds = context(1024, 900, {dtype!r}), ctypes.c_void_p(4 << 40), ctypes.c_void_p(5 << 40)
+    size = lib.sslbm_fd4_workspace_bytes(h)
+    rec.rec_device(there)
+    row = []
+    for call in (lambda: lib.bgk_run(h, rho, d, scratch, ds, 30, None),
+                 lambda: lib.sslbm_fd4_run(h, rho, scratch, size, 4, None),
+                 lambda: lib.sslbm_run(h, rho, scratch, 30, None)):
+        rec.rec_clear()
+        row.append([call(), [l[:3] for l in launched()]])
+    calls.append(row)
+result = calls
+''')
+    asked, unasked = result
+    assert [c[0] for c in asked + unasked] == 6 * [0]
+    assert unasked[:2] == asked[:2] and unasked[2][1]
