@@ -249,3 +249,33 @@ result = calls
     asked, unasked = result
     assert [c[0] for c in asked + unasked] == 6 * [0]
     assert unasked[:2] == asked[:2] and unasked[2][1]
+
+
+@pytest.mark.parametrize("d_dead", [0.0, 3e-3])
+def test_compared_sizes_take_every_tile_height(d_dead):
+    """The sizes whose tiles the GPU tests compare with the march cover every
+    tile height there is, on single grids and in ensembles."""
+    from test_gpu_ensemble_tiles import HEIGHTS
+    single, many = record(f'''
+single = {{}}
+for dtype in ("f32", "f64"):
+    rows = set()
+    for nx, ny, steps in {_tile_shapes()!r}:
+        h = context(nx, ny, dtype, {d_dead})
+        rows |= {{k[2] for k in passes(lambda: lib.sslbm_run(h, rho, scratch, steps, None))
+                 if k[0] == "tile"}}
+    single[dtype] = sorted(rows)
+many = []
+for dtype, rows, steps, sizes in {HEIGHTS!r}:
+    e = ensemble(sizes, dtype, {d_dead})
+    kinds = passes(lambda: lib.sslbm_ensemble_run(e, rho, scratch, steps, 0, None))
+    many.append([dtype, *sorted({{k[2] for k in kinds if k[0] == "tile"}})])
+result = [single, many]
+''')
+    assert single == {"f32": [2, 3, 4, 5, 7], "f64": [1, 2, 3]}
+    assert many == [[dtype, rows] for dtype, rows, *_ in HEIGHTS]
+
+
+def _tile_shapes():
+    from test_gpu_tiles import SHAPES
+    return SHAPES
