@@ -68,7 +68,6 @@ TRAFFIC_FILE = ROOT / "profiles" / "sslbm_march_4096_traffic.md"
 # algorithmic HBM bytes per node and step at one step per pass
 SSLBM_BYTES = {"f32": 40, "f64": 80}      # 5 fields read + 5 written
 BGK_BYTES = {"f32": 168, "f64": 336}      # 20 populations + rhoD, read + written
-BGK_DEPTH = {"f32": 7, "f64": 3}          # steps per HBM pass of bgk_run on the 4096^2 grid
 
 
 def parse_args():
@@ -140,15 +139,6 @@ def march_kernel(dtype, k, cols_per_lane):
     return f"sslbm_march_kernel<{t}, {k}, false, {cols_per_lane}>"
 
 
-def even_passes(steps, depth):
-    """The pass plan of a run of `steps` steps at up to `depth` per pass: the
-    fewest passes, made even while each keeps a step, the steps spread evenly."""
-    count = -(-steps // depth)
-    if count % 2 and count < steps:
-        count += 1
-    return {"passes": count, "longest": -(-steps // count), "shortest": steps // count}
-
-
 def run_variant(torch, scheme, dtype, r0, steps, warmup, inputs, Solver, BGK, depth=0,
                 repeats=1):
     """One scheme / type / R0 on the 4096 x 4096 workload: `warmup` untimed
@@ -179,7 +169,7 @@ def run_variant(torch, scheme, dtype, r0, steps, warmup, inputs, Solver, BGK, de
         solver = BGK(NX, NY, params, dtype=dtype)
         f, rd = solver.init(torch.tensor(rho0, dtype=tdt, device="cuda"))
         fs, ds = torch.empty_like(f), torch.empty_like(rd)
-        plan = even_passes(steps, BGK_DEPTH[dtype])
+        plan = solver.plan(steps)
         shape = {"steps_per_pass": plan["longest"]}
 
         def timed():

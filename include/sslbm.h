@@ -248,6 +248,7 @@ sslbm_status sslbm_plan_run(const sslbm_ctx *c, long long nsteps, long long *pas
  *                (passes of one or several steps alternate between the two;
  *                an odd number of passes, as one single step, ends with a
  *                copy of the state from the scratch into f/rhoD).
+ *   bgk_plan_run: how bgk_run splits nsteps into passes, as sslbm_plan_run.
  *   bgk_density: rho[C] = sum_i f_i for S, E, I, R and rho[D] = rhoD.
  */
 sslbm_status bgk_init(sslbm_ctx *c, const void *rho, void *f, void *rhoD, void *hip_stream);
@@ -255,6 +256,8 @@ sslbm_status bgk_step(sslbm_ctx *c, const void *f_in, const void *rhoD_in, void 
                       void *rhoD_out, void *hip_stream);
 sslbm_status bgk_run(sslbm_ctx *c, void *f, void *rhoD, void *f_scratch, void *rhoD_scratch,
                      long long nsteps, void *hip_stream);
+sslbm_status bgk_plan_run(const sslbm_ctx *c, long long nsteps, long long *passes, int *longest,
+                          int *shortest);
 sslbm_status bgk_density(sslbm_ctx *c, const void *f, const void *rhoD, void *rho,
                          void *hip_stream);
 

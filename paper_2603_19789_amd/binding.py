@@ -103,6 +103,7 @@ def library() -> ctypes.CDLL:
             "sslbm_step": [vp, vp, vp, vp],
             "sslbm_run": [vp, vp, vp, ll, vp],
             "sslbm_plan_run": [vp, ll, ctypes.POINTER(ll), ctypes.POINTER(i), ctypes.POINTER(i)],
+            "bgk_plan_run": [vp, ll, ctypes.POINTER(ll), ctypes.POINTER(i), ctypes.POINTER(i)],
             "bgk_init": [vp, vp, vp, vp, vp],
             "bgk_step": [vp, vp, vp, vp, vp, vp],
             "bgk_run": [vp, vp, vp, vp, vp, ll, vp],
@@ -254,6 +255,12 @@ class _Context:
         if st != OK:
             raise SSLBMError(st, what, self.lib.sslbm_last_hip_error(self.handle))
 
+    def _plan(self, name, nsteps):
+        n, hi, lo = ctypes.c_longlong(), ctypes.c_int(), ctypes.c_int()
+        self._check(getattr(self.lib, name)(self.handle, int(nsteps), ctypes.byref(n),
+                                            ctypes.byref(hi), ctypes.byref(lo)), name)
+        return {"passes": n.value, "longest": hi.value, "shortest": lo.value}
+
     def _tensor(self, t, shape, name):
         torch = _torch()
         if not isinstance(t, torch.Tensor):
@@ -349,11 +356,7 @@ class Solver(_Context):
     def plan(self, nsteps: int) -> dict:
         """How `run` splits nsteps into passes with the current pass shape:
         {"passes", "longest", "shortest"} (host only)."""
-        n, hi, lo = ctypes.c_longlong(), ctypes.c_int(), ctypes.c_int()
-        self._check(self.lib.sslbm_plan_run(self.handle, int(nsteps), ctypes.byref(n),
-                                            ctypes.byref(hi), ctypes.byref(lo)),
-                    "sslbm_plan_run")
-        return {"passes": n.value, "longest": hi.value, "shortest": lo.value}
+        return self._plan("sslbm_plan_run", nsteps)
 
     def total(self, rho, stream=None):
         """Per-compartment totals (5 floats, FP64 sums); waits for the stream."""
@@ -511,6 +514,10 @@ class BGK(_Context):
                                      self._tensor(rhoD_scratch, plane, "rhoD_scratch"),
                                      int(nsteps), _stream(stream)), "bgk_run")
         return f, rhoD
+
+    def plan(self, nsteps: int) -> dict:
+        """How `run` splits nsteps into passes, as `Solver.plan`."""
+        return self._plan("bgk_plan_run", nsteps)
 
     def density(self, f, rhoD, rho=None, stream=None):
         if rho is None:

@@ -513,18 +513,21 @@ sslbm_status sslbm_tune(sslbm_ctx *c, const void *rho, void *scratch, void *hip_
     return SSLBM_OK;
 }
 
-sslbm_status sslbm_plan_run(const sslbm_ctx *c, long long nsteps, long long *passes, int *longest,
-                            int *shortest) {
-    if (!c || nsteps < 0 || !passes)
-        return SSLBM_E_ARG;
-    const sslbm::TilePlan tiles = run_tiles(c, nsteps);
-    const sslbm::PassPlan p =
-        sslbm::plan_passes(nsteps, tiles.rows ? tiles.depth : resolve(c).steps_per_pass);
+static void report_plan(const sslbm::PassPlan &p, long long *passes, int *longest, int *shortest) {
     *passes = p.count;
     if (longest)
         *longest = p.count == 0 ? 0 : p.steps(0);
     if (shortest)
         *shortest = p.count == 0 ? 0 : p.steps(p.count - 1);
+}
+
+sslbm_status sslbm_plan_run(const sslbm_ctx *c, long long nsteps, long long *passes, int *longest,
+                            int *shortest) {
+    if (!c || nsteps < 0 || !passes)
+        return SSLBM_E_ARG;
+    const sslbm::TilePlan tiles = run_tiles(c, nsteps);
+    report_plan(sslbm::plan_passes(nsteps, tiles.rows ? tiles.depth : resolve(c).steps_per_pass),
+                passes, longest, shortest);
     return SSLBM_OK;
 }
 
@@ -627,6 +630,21 @@ sslbm_status bgk_step(sslbm_ctx *c, const void *f_in, const void *rhoD_in, void 
                                                 grid_of(c), c->coef, (hipStream_t)hip_stream));
 }
 
+static sslbm::PassPlan bgk_passes(const sslbm_ctx *c, long long nsteps) {
+    return sslbm::plan_passes(nsteps, sslbm::bgk_depth(c->dtype, grid_of(c)));
+}
+
+sslbm_status bgk_plan_run(const sslbm_ctx *c, long long nsteps, long long *passes, int *longest,
+                          int *shortest) {
+    const sslbm_status st = bgk_check(c);
+    if (st != SSLBM_OK)
+        return st;
+    if (nsteps < 0 || !passes)
+        return SSLBM_E_ARG;
+    report_plan(bgk_passes(c, nsteps), passes, longest, shortest);
+    return SSLBM_OK;
+}
+
 sslbm_status bgk_run(sslbm_ctx *c, void *f, void *rhoD, void *f_scratch, void *rhoD_scratch,
                      long long nsteps, void *hip_stream) {
     sslbm_status st = bgk_check(c);
@@ -644,7 +662,7 @@ sslbm_status bgk_run(sslbm_ctx *c, void *f, void *rhoD, void *f_scratch, void *r
     const hipStream_t s = (hipStream_t)hip_stream;
     const sslbm::GridDesc g = grid_of(c);
     void *fa = f, *da = rhoD, *fb = f_scratch, *db = rhoD_scratch;
-    const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, sslbm::bgk_depth(c->dtype, g));
+    const sslbm::PassPlan plan = bgk_passes(c, nsteps);
     for (long long i = 0; i < plan.count; ++i) {
         st = hip_status(c, sslbm::launch_bgk_pass(c->dtype, fa, da, fb, db, g, c->coef,
                                                   plan.steps(i), s));

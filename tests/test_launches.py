@@ -191,6 +191,31 @@ for nx, ny, *_ in {cases!r}:
     assert result == [list(c) for c in cases]
 
 
+def test_reported_bgk_plan_is_the_run_s():
+    """BGK.plan, which the benchmark reports passes and traffic by, against the
+    passes that are launched."""
+    result = record('''
+from paper_2603_19789_amd import BGK
+result = []
+for nx, ny in ((64, 64), (400, 400), (1100, 900), (4096, 4096), (200000, 1)):
+    for dtype in ("f32", "f64"):
+        b, d, ds = BGK(nx, ny, params(), dtype), ctypes.c_void_p(4 << 40), ctypes.c_void_p(5 << 40)
+        for steps in (0, 1, 2, 7, 20, 63):
+            kinds = passes(lambda: lib.bgk_run(b.handle, rho, d, scratch, ds, steps, None))
+            took = [k[1] for k in kinds if k[0] == "bgk"]
+            p = b.plan(steps)
+            result.append([[len(took), max(took, default=0), min(took, default=0)],
+                           [p["passes"], p["longest"], p["shortest"]]])
+n = ctypes.c_longlong()
+h, mobile = context(64, 64), context(64, 64, d_dead=1e-3)
+result.append([[lib.bgk_plan_run(h, -1, ctypes.byref(n), None, None),
+                lib.bgk_plan_run(h, 1, None, None, None),
+                lib.bgk_plan_run(None, 1, ctypes.byref(n), None, None),
+                lib.bgk_plan_run(mobile, 1, ctypes.byref(n), None, None)], [-1, -1, -1, -3]])
+''')
+    assert all(a == b for a, b in result), result
+
+
 def test_rows_of_small_ensembles():
     """Automatic rows per wavefront of ensembles just too large for tiles: the
     faster of one and two wavefronts a SIMD, not a fixed least height."""
