@@ -211,8 +211,10 @@ int rows_for(const std::vector<sslbm::GridSize> &sizes, int w, long long tiles, 
 // 392 at 16; 6 of them 325 at 12 rows, 290 at 16 and one wavefront).
 int auto_rows(const sslbm_ensemble *e, const std::vector<sslbm::GridSize> &sizes, int K, int V) {
     long long resident = sslbm::march_resident_waves(e->dtype, K, V, e->diffuse_d);
-    if (resident <= 0)
+    if (resident <= 0) {
+        (void)hipGetLastError();  // the query's error is not the launch's
         resident = 2 * 4 * 256;
+    }
     const int w = sslbm::strip_width(K, V), least = 2 * K, most = e->march_max_side;
     int best = rows_for(sizes, w, resident, least, most);
     if (best >= 16)

@@ -65,8 +65,10 @@ long long round_rows(const sslbm_ctx *c, int K, int V) {
     const int w = sslbm::strip_width(K, V);
     const long long strips = (c->nx + w - 1) / w;
     long long resident = sslbm::march_resident_waves(c->dtype, K, V, c->coef.diffuse_d);
-    if (resident <= 0)
+    if (resident <= 0) {
+        (void)hipGetLastError();  // the query's error is not the launch's
         resident = 3 * 4 * 256;
+    }
     long long chunks = resident / strips;
     if (chunks < 1)
         chunks = 1;

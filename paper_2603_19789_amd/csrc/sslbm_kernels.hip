@@ -169,10 +169,8 @@ int march_resident_waves(int dtype, int K, int cols_per_lane, bool diffuse_d) {
     static int cache[16][2][2][SSLBM_MAX_BLOCKING + 1][2] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16 || K < 1 ||
-        K > SSLBM_MAX_BLOCKING || cols_per_lane < 1 || cols_per_lane > 2) {
-        (void)hipGetLastError();
+        K > SSLBM_MAX_BLOCKING || cols_per_lane < 1 || cols_per_lane > 2)
         return 0;
-    }
     int &slot = cache[dev][dtype == SSLBM_F64][cols_per_lane - 1][K][diffuse_d ? 1 : 0];
     if (slot)
         return slot;
