@@ -275,7 +275,7 @@ sslbm_status bgk_density(sslbm_ctx *c, const void *f, const void *rhoD, void *rh
  * whose real extent is 2.78).
  *
  *   sslbm_fd4_workspace_bytes: bytes of the workspace sslbm_fd4_run needs
- *       (three states), 0 for a null context.
+ *       (three states, of which the steps use two), 0 for a null context.
  *   sslbm_fd4_run: nsteps steps in place in rho (device, layout as
  *       sslbm_step), work a device buffer of work_bytes >= the workspace
  *       size, caller-owned and clobbered. SSLBM_E_ARG for null pointers,

@@ -9,7 +9,8 @@
 namespace sslbm {
 
 // nsteps RK4 steps of the fourth-order finite-difference system, in place
-// in rho; work holds three states (two stage inputs and the running sum).
+// in rho. work holds three states, as callers have always given it; steps go
+// between rho and its first two.
 hipError_t launch_fd4(int dtype, void *rho, void *work, const GridDesc &g, const StepCoef &k,
                       long long nsteps, hipStream_t s);
 
