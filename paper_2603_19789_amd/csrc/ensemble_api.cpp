@@ -21,8 +21,10 @@
 //    pass and columns per lane (the automatic shapes do, as a rule): one
 //    launch per pass fills the GPU by itself, while a stream per class shares
 //    hardware queues with the others, so that classes wait for each other
-//    (96 grids of 64^2 to 512^2, FP32: 4.9 ms for 200 steps with three march
-//    chains, 3.0 ms with one);
+//    (96 grids of 64^2 to 512^2, the smallest on chip, FP32: 4.9 ms for 200
+//    steps with three march chains, 3.5 ms with one);
+//  * one such chain with one column per lane and one with two, on large
+//    ensembles some of whose classes have grids of odd rows;
 //  * else a chain per class.
 #include <hip/hip_runtime_api.h>
 
@@ -169,21 +171,27 @@ long long count_tiles(const std::vector<sslbm::GridSize> &sizes, int w, int H) {
     return n;
 }
 
-// Automatic columns per lane of the march classes, one number for all of them
-// (so that they can share a launch): two halve the shifts per cell (about 7%:
-// 40 grids of 512^2 556 against 519 GLUPS), unless their strips, twice as
-// wide, cover more columns past the edges than that (256^2: 293 against 352;
-// 128^2 to 512^2 mixed: 443 against 474).
-int auto_cols(const sslbm_ensemble *e, int K) {
+// Automatic columns per lane of grids of some sizes that share a launch: two
+// halve the shifts per cell (about 5%: 40 grids of 512^2 555 against 527 GLUPS),
+// unless their strips, twice as wide, cover more columns past the edges than
+// that (256^2: 399 against 454; 64^2 to 512^2 mixed: 481 against 487).
+int auto_cols(const sslbm_ensemble *e, const std::vector<sslbm::GridSize> &sizes, int K) {
     if (e->dtype != SSLBM_F32 || K > sslbm::march_max_depth(e->dtype, 2))
         return 1;
     long long covered[2] = {0, 0};
     for (int V = 1; V <= 2; ++V) {
         const int w = sslbm::strip_width(K, V);
-        for (const sslbm::GridSize &z : e->march_sizes)
+        for (const sslbm::GridSize &z : sizes)
             covered[V - 1] += (long long)((z.nx + w - 1) / w) * 64 * V * z.ny * z.count;
     }
     return covered[1] <= covered[0] + covered[0] / 32 ? 2 : 1;
+}
+
+long long cells_of(const std::vector<sslbm::GridSize> &sizes) {
+    long long n = 0;
+    for (const sslbm::GridSize &z : sizes)
+        n += (long long)z.nx * z.ny * z.count;
+    return n;
 }
 
 // The fewest rows per wavefront, at least `least`, for which the tiles of grids
@@ -205,7 +213,7 @@ int rows_for(const std::vector<sslbm::GridSize> &sizes, int w, long long tiles, 
 // the fewest for which all their tiles are resident at once, the same rows for
 // every class of a pass (it lasts as long as its longest march; with rows by
 // each class's share of the GPU the smallest class had the tallest ones, and 96
-// grids of 64^2 to 512^2 took 390 GLUPS). Where that gives chunks of fewer than
+// grids of 64^2 to 512^2 ran at 390 GLUPS, 481 so). Where that gives chunks of fewer than
 // 16 rows, a wavefront less per SIMD on taller ones may be faster, as estimated
 // (FP32, 60 steps: 8 grids of 512^2 330 us at 12 rows and two wavefronts a SIMD,
 // 392 at 16; 6 of them 325 at 12 rows, 290 at 16 and one wavefront).
@@ -232,25 +240,73 @@ int auto_rows(const sslbm_ensemble *e, const std::vector<sslbm::GridSize> &sizes
     return best;
 }
 
+// Sizes of the march classes whose rows are all even (even = true), or of the
+// others.
+std::vector<sslbm::GridSize> sizes_by_parity(const sslbm_ensemble *e, bool even) {
+    std::vector<sslbm::GridSize> out;
+    for (const EnsClass &cl : e->classes)
+        if (!cl.on_chip && cl.even_rows == even)
+            out.insert(out.end(), cl.sizes.begin(), cl.sizes.end());
+    return out;
+}
+
+// Whether classes of even rows take two columns per lane in a chain of their
+// own while others, which cannot, keep one. One launch for all leaves every
+// class at one column, but two chains share the GPU badly where passes are
+// short: of 97 mixes of 4 to 30 million cells, 60 steps, two chains were up to
+// 29% slower at 4 million (256^2 beside 301^2 606 us, one chain 470) and even on
+// the mean at 12 million (60 rows a wavefront), but up to 15% faster at 30
+// million (130 to 200 rows: 21 grids of 1024^2 and 29 of 511^2 3066 us, one
+// chain 3640) and 7% at 86 rows, unless the even grids are few or do not gain by
+// two columns.
+bool cols_by_class(const sslbm_ensemble *e, int K, bool pairs_ok) {
+    constexpr int TALL = 80;
+    if (!pairs_ok || e->dtype != SSLBM_F32)
+        return false;
+    const std::vector<sslbm::GridSize> even = sizes_by_parity(e, true);
+    if (even.empty() || cells_of(even) * 4 < cells_of(e->march_sizes) ||
+        sizes_by_parity(e, false).empty() || auto_cols(e, even, K) == 1)
+        return false;
+    return auto_rows(e, e->march_sizes, K, 1) >= TALL;
+}
+
+// Rows of one of two chains: the fewest for which its tiles fit its share of
+// the resident wavefronts, by cells.
+int shared_rows(const sslbm_ensemble *e, bool even, int K, int V) {
+    const std::vector<sslbm::GridSize> sizes = sizes_by_parity(e, even);
+    const double share = (double)cells_of(sizes) / (double)cells_of(e->march_sizes);
+    const double resident = (double)sslbm::march_resident_waves(e->dtype, K, V, e->diffuse_d);
+    const long long tiles = std::max(64ll, (long long)(share * (resident > 0 ? resident : 2048.)));
+    return rows_for(sizes, sslbm::strip_width(K, V), tiles, 2 * K, e->march_max_side);
+}
+
 // Pass shape of march class c: requested fields, automatic ones filled in.
 // Automatic: six steps in FP32, five in FP64; columns and rows as above, over
-// every march class (over class c alone where it runs alone).
+// every march class (over class c alone where it runs alone). With a diffusing
+// D too five steps in FP64, although that kernel spills and small single grids
+// take four: 60 steps of 96 grids of 64^2 to 512^2 2025 us, 2403 at four; 200 of
+// 128^2 1076 and 1108; four win only below 3 million cells (8 of 512^2 573, 545).
 sslbm_launch resolve(const sslbm_ensemble *e, int c, bool pairs_ok = true, bool alone = false) {
     const EnsClass &cl = e->classes[c];
     sslbm_launch r = cl.launch;
     if (r.steps_per_pass == 0)
         r.steps_per_pass = e->dtype == SSLBM_F32 ? 6 : 5;
-    if (r.cols_per_lane == 0) {
-        r.cols_per_lane = auto_cols(e, r.steps_per_pass);
-        for (int i = 0; i < (int)e->classes.size(); ++i)
-            if (!e->classes[i].on_chip)
-                r.cols_per_lane = std::min(
-                    r.cols_per_lane, usable_cols(e, i, r.cols_per_lane, r.steps_per_pass, pairs_ok));
+    const int K = r.steps_per_pass;
+    if (r.cols_per_lane == 0 && !alone && cols_by_class(e, K, pairs_ok)) {
+        r.cols_per_lane = cl.even_rows ? 2 : 1;
+        if (r.rows_per_wave == 0)
+            r.rows_per_wave = shared_rows(e, cl.even_rows, K, r.cols_per_lane);
     }
-    r.cols_per_lane = usable_cols(e, c, r.cols_per_lane, r.steps_per_pass, pairs_ok);
+    if (r.cols_per_lane == 0) {
+        r.cols_per_lane = auto_cols(e, alone ? cl.sizes : e->march_sizes, K);
+        for (int i = 0; i < (int)e->classes.size(); ++i)
+            if (!e->classes[i].on_chip && !alone)
+                r.cols_per_lane =
+                    std::min(r.cols_per_lane, usable_cols(e, i, r.cols_per_lane, K, pairs_ok));
+    }
+    r.cols_per_lane = usable_cols(e, c, r.cols_per_lane, K, pairs_ok);
     if (r.rows_per_wave == 0)
-        r.rows_per_wave =
-            auto_rows(e, alone ? cl.sizes : e->march_sizes, r.steps_per_pass, r.cols_per_lane);
+        r.rows_per_wave = auto_rows(e, alone ? cl.sizes : e->march_sizes, K, r.cols_per_lane);
     return r;
 }
 
@@ -368,7 +424,7 @@ std::vector<Chain> march_chains(const sslbm_ensemble *e, long long nsteps, bool 
                                 int *pay) {
     std::vector<Chain> out;
     bool automatic = true, alike = true;
-    sslbm_launch joint{};  // the shape of every class with automatic ones
+    sslbm_launch joint[2] = {};  // the shapes of classes with automatic ones, by even rows
     for (int c = 0; c < (int)e->classes.size(); ++c) {
         const EnsClass &cl = e->classes[c];
         if (cl.on_chip)
@@ -376,9 +432,10 @@ std::vector<Chain> march_chains(const sslbm_ensemble *e, long long nsteps, bool 
         const bool own = cl.launch.steps_per_pass == 0 && cl.launch.rows_per_wave == 0 &&
                          cl.launch.cols_per_lane == 0;
         automatic = automatic && own;
-        const sslbm_launch r = own && joint.steps_per_pass ? joint : resolve(e, c, pairs_ok);
+        sslbm_launch &kept = joint[cl.even_rows];
+        const sslbm_launch r = own && kept.steps_per_pass ? kept : resolve(e, c, pairs_ok);
         if (own)
-            joint = r;
+            kept = r;
         Chain ch;
         ch.classes = {c};
         ch.K = r.steps_per_pass;
@@ -387,18 +444,24 @@ std::vector<Chain> march_chains(const sslbm_ensemble *e, long long nsteps, bool 
         alike = alike && (out.empty() || (out[0].K == ch.K && out[0].V == ch.V));
         out.push_back(ch);
     }
-    if (out.empty())
-        return out;
-    // automatic shapes are alike
-    if (alike) {
-        for (size_t i = 1; i < out.size(); ++i) {
-            out[0].classes.push_back(out[i].classes[0]);
-            out[0].H.push_back(out[i].H[0]);
+    // classes alike in one chain; automatic shapes are alike but for the columns
+    // of even rows (cols_by_class): two chains
+    if (alike || automatic) {
+        std::vector<Chain> merged;
+        for (const Chain &ch : out) {
+            auto m = std::find_if(merged.begin(), merged.end(),
+                                  [&](const Chain &o) { return o.K == ch.K && o.V == ch.V; });
+            if (m == merged.end()) {
+                merged.push_back(ch);
+            } else {
+                m->classes.push_back(ch.classes[0]);
+                m->H.push_back(ch.H[0]);
+            }
         }
-        out.resize(1);
-        if (automatic)
-            out[0].tiles = chain_tiles(e, e->march_sizes, out[0], nsteps, pay);
+        out.swap(merged);
     }
+    if (automatic && out.size() == 1)
+        out[0].tiles = chain_tiles(e, e->march_sizes, out[0], nsteps, pay);
     return out;
 }
 

@@ -232,6 +232,40 @@ for n, side, _ in {cases!r}:
     assert result == [list(c) for c in cases]
 
 
+# (sizes and counts, kernels' columns a lane, chains): one chain at one column
+# where the classes of odd rows hold most cells, where passes are short or where
+# two columns cover more; else a chain of the even classes at two
+MIXED = [([(1024, 1024, 14), (511, 511, 57)], [1, 2]), ([(1024, 1024, 16), (333, 333, 4)], [1, 2]),
+         ([(2048, 2048, 4), (511, 300, 1), (200, 100, 3)], [1, 2]),
+         ([(1024, 1024, 7), (1025, 1025, 40)], [1]), ([(400, 400, 30), (201, 201, 30)], [1]),
+         ([(256, 256, 412), (301, 301, 33)], [1]), ([(1024, 1024, 20), (512, 512, 20)], [2]),
+         ([(1025, 1025, 20), (511, 512, 20)], [1])]
+
+
+def test_columns_of_ensembles_with_odd_rows():
+    """Classes of even rows keep two columns a lane beside odd ones on large
+    ensembles; a class that runs alone takes the columns of its own sizes."""
+    result = record(f'''
+result = []
+for groups, want in {MIXED!r}:
+    sizes = [(nx, ny) for nx, ny, n in groups for _ in range(n)]
+    e = ensemble(sizes)
+    passes(lambda: lib.sslbm_ensemble_run(e, rho, scratch, 12, 0, None))
+    ks = [l for l in launched() if l[0] == "ensemble_march_kernel"]
+    alone = []
+    for c in range(lib.sslbm_ensemble_class_count(e)):
+        passes(lambda: lib.sslbm_ensemble_run_class(e, c, rho, scratch, 12, None))
+        alone += [int(l[1][3]) for l in launched() if l[0] == "ensemble_march_kernel"][:1]
+    double = ensemble(sizes, "f64")
+    passes(lambda: lib.sslbm_ensemble_run(double, rho, scratch, 20, 0, None))
+    f64 = [l for l in launched() if l[0] == "ensemble_march_kernel"]
+    result.append([want, sorted({{int(l[1][3]) for l in ks}}), len(ks), alone, len(f64)])
+''')
+    for want, cols, count, alone, f64 in result:
+        assert cols == want and count == 2 * len(want) and f64 == 4, (want, cols, count, f64)
+    assert result[0][3] == [1, 2] and result[3][3] == [2, 1]  # by class, in order of size
+
+
 def test_an_ensemble_run_is_planned_once():
     """A run that repeats the last one's steps makes no new plan; one with other
     steps, or after a change of shapes, does."""
