@@ -403,6 +403,32 @@ double march_step_us(const sslbm_ensemble *e, const Chain &ch) {
     return sslbm::march_us(e->dtype, ch.K, ch.V, rows, waves) / ch.K;
 }
 
+// Whether a run of a few steps is estimated to be faster by a chain's marches.
+bool short_marches(const sslbm_ensemble *e, const std::vector<sslbm::GridSize> &sizes,
+                   const Chain &ch, const sslbm::TilePlan &tiles, long long nsteps) {
+    if (nsteps > sslbm::SHORT_RUN)
+        return false;
+    for (const sslbm::GridSize &z : sizes)
+        if (std::min(z.nx, z.ny) < sslbm::SHORT_RUN_SIDE)
+            return false;
+    auto one = [&](int k) {
+        const int w = sslbm::strip_width(k, ch.V);
+        long long waves = 0;
+        int rows = 0;
+        for (size_t i = 0; i < ch.classes.size(); ++i) {
+            waves += count_tiles(e->classes[ch.classes[i]].sizes, w, ch.H[i]);
+            rows = std::max(rows, ch.H[i]);
+        }
+        return sslbm::short_march_us(e->dtype, k, ch.V, rows, waves, cells_of(sizes));
+    };
+    const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, ch.K);
+    double march = (double)(plan.count - plan.longer) * one(plan.base);
+    if (plan.longer)
+        march += (double)plan.longer * one(plan.base + 1);
+    return sslbm::short_tiles_us(e->dtype, sizes.data(), (int)sizes.size(), tiles.rows,
+                                 sslbm::plan_passes(nsteps, tiles.depth)) > 1.03 * march;
+}
+
 // Tiles of a chain whose shapes are all automatic: as for a single grid, none
 // where its grids are too large for them or the march is estimated to be faster
 // (an answer for runs of every length, kept in *pay, -1 before).
@@ -414,6 +440,8 @@ sslbm::TilePlan chain_tiles(const sslbm_ensemble *e, const std::vector<sslbm::Gr
     const sslbm::TilePlan tiles = sslbm::tile_plan(e->dtype, sizes.data(), n, nsteps);
     if (tiles.rows == 0 || tiles.few || e->tiles_tuned)
         return tiles;
+    if (short_marches(e, sizes, ch, tiles, nsteps))
+        return sslbm::TilePlan();
     if (*pay < 0)
         *pay = sslbm::tiles_pay(e->dtype, sizes.data(), n, march_step_us(e, ch)) ? 1 : 0;
     return *pay ? tiles : sslbm::TilePlan();

@@ -3,6 +3,7 @@
 // Every check runs before the first HIP call, so rejected calls need no GPU.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -132,6 +133,16 @@ sslbm_launch resolve(const sslbm_ctx *c) {
     return r;
 }
 
+// Most steps of a march pass in a run of nsteps. A segment that one wavefront can
+// hold is one pass, whatever the context's steps per pass: a state less through
+// HBM each way than in two passes (FP32 4096^2 every 8 steps: 2247 us for 64
+// steps, 2741 in passes of four; FP64 with a diffusing D every 5: 2827 us for 40
+// steps although that kernel spills, 5449 in passes of three and two).
+int march_depth(const sslbm_ctx *c, long long nsteps, bool segment) {
+    return segment && nsteps <= sslbm::march_max_depth(c->dtype, 1) ? (int)nsteps
+                                                                    : resolve(c).steps_per_pass;
+}
+
 // Tiles of a run of nsteps (of a segment: with the fewest passes): none (rows =
 // 0) where the caller has chosen a march shape, the grid is too large for them,
 // or the march is estimated to be faster. That is the case on grids a few cells
@@ -140,6 +151,7 @@ sslbm_launch resolve(const sslbm_ctx *c) {
 // few cells wide (FP64 1 x 70000: 1026 and 631), and at sizes whose march just
 // fills its wavefronts (FP32 1101^2: 239 and 211). A context that was tuned and
 // is still on automatic shapes takes tiles: they were the faster when timed.
+// Runs of a few steps are estimated by themselves besides.
 sslbm::TilePlan run_tiles(const sslbm_ctx *c, long long nsteps, bool fewest = false) {
     if (!automatic(c->launch))
         return sslbm::TilePlan();
@@ -148,11 +160,36 @@ sslbm::TilePlan run_tiles(const sslbm_ctx *c, long long nsteps, bool fewest = fa
     if (tiles.rows == 0 || tiles.few || c->tuned.steps_per_pass > 0)
         return tiles;
     const sslbm_launch r = resolve(c);
-    const int K = r.steps_per_pass, V = c->nx % 2 == 0 ? r.cols_per_lane : 1;
-    const int rows = auto_rows(c, K, V), w = sslbm::strip_width(K, V);
-    const long long waves =
-        (long long)((c->nx + w - 1) / w) * ((c->ny + rows - 1) / rows);
-    const double march = sslbm::march_us(c->dtype, K, V, rows, waves) / K;
+    struct Pass {
+        int K, V, rows;
+        long long waves;
+    };
+    auto pass = [&](int k) {
+        Pass p{k, c->nx % 2 == 0 && k <= sslbm::march_max_depth(c->dtype, 2) ? r.cols_per_lane : 1};
+        const int w = sslbm::strip_width(k, p.V);
+        p.rows = auto_rows(c, k, p.V);
+        p.waves = (long long)((c->nx + w - 1) / w) * ((c->ny + p.rows - 1) / p.rows);
+        return p;
+    };
+    if (nsteps <= sslbm::SHORT_RUN && std::min(c->nx, c->ny) >= sslbm::SHORT_RUN_SIDE) {
+        auto passes = [&](int K) {
+            return fewest ? sslbm::fewest_passes(nsteps, K) : sslbm::plan_passes(nsteps, K);
+        };
+        auto one = [&](int k) {
+            const Pass p = pass(k);
+            return sslbm::short_march_us(c->dtype, k, p.V, p.rows, p.waves,
+                                         (long long)plane_elems(c));
+        };
+        const sslbm::PassPlan plan = passes(march_depth(c, nsteps, fewest));
+        double march = (double)(plan.count - plan.longer) * one(plan.base);
+        if (plan.longer)
+            march += (double)plan.longer * one(plan.base + 1);
+        if (sslbm::short_tiles_us(c->dtype, &size, 1, tiles.rows, passes(tiles.depth)) >
+            1.03 * march)
+            return sslbm::TilePlan();
+    }
+    const Pass p = pass(r.steps_per_pass);
+    const double march = sslbm::march_us(c->dtype, p.K, p.V, p.rows, p.waves) / p.K;
     return sslbm::tiles_pay(c->dtype, &size, 1, march) ? tiles : sslbm::TilePlan();
 }
 
@@ -186,14 +223,7 @@ sslbm_status run_pass(sslbm_ctx *c, const void *in, void *out, int k, hipStream_
 SegmentShape segment_shape(const sslbm_ctx *c, long long n) {
     SegmentShape shape;
     shape.tiles = run_tiles(c, n, true);
-    // A march takes a segment that one wavefront can hold in one pass,
-    // whatever the context's steps per pass: a state less through HBM each way
-    // than in two passes (FP32 4096^2 every 8 steps: 2247 us for 64 steps, 2741
-    // in passes of four; FP64 with a diffusing D every 5: 2827 us for 40 steps
-    // although that kernel spills, 5449 in passes of three and two).
-    shape.depth = shape.tiles.rows                      ? shape.tiles.depth
-                  : n <= march_max_depth(c->dtype, 1) ? (int)n
-                                                        : resolve(c).steps_per_pass;
+    shape.depth = shape.tiles.rows ? shape.tiles.depth : march_depth(c, n, true);
     return shape;
 }
 

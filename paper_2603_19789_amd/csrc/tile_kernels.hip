@@ -107,6 +107,46 @@ TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps, bo
     return best;
 }
 
+// Runs of a few steps move the state at least twice for little work, so they
+// have a fit of their own, with the cells read and written (in millions): 27
+// grids of 64^2 to 1.4 million cells and at least 64 each way, 2 to 24 steps,
+// 6% rms. With the faster of the two by these estimates, such runs are within
+// 0.4% of the faster kind on the mean and 12% at most; with tiles wherever a
+// long run takes them it was 7% and 45% (5 steps, FP32: 1500 x 901 30.1 us of
+// tiles, 23.2 of marches; 1024^2 23.9 and 20.8; 768^2 16.2 and 14.7).
+double short_tiles_us(int dtype, const GridSize *sizes, int n, int R, const PassPlan &plan) {
+    const int cus = compute_units();
+    long long cells = 0;
+    for (int i = 0; i < n; ++i)
+        cells += (long long)sizes[i].nx * sizes[i].ny * sizes[i].count;
+    const double mega = 1e-6 * (double)cells;
+    auto pass = [&](int k) {
+        long long tiles = 0;
+        for (int i = 0; i < n; ++i)
+            tiles += tile_count(sizes[i].nx, sizes[i].ny, R, k) * sizes[i].count;
+        int rows = 0;
+        for (int s = 1; s <= k; ++s)
+            rows += (TILE_WAVES - 2 * (s / R)) * R / 4;
+        const double rounds = (double)((tiles + cus - 1) / cus);
+        return dtype == SSLBM_F32 ? 2.46 + 0.289 * k + 0.075 * rounds * rows + 4.76 * mega
+                                  : 0.295 * k + rounds * (3.0 + 0.139 * rows) + 8.31 * mega;
+    };
+    // (no pass is deeper than the tile allows)
+    return (plan.longer ? (double)plan.longer * pass(plan.base + 1) : 0.0) +
+           (double)(plan.count - plan.longer) * pass(plan.base);
+}
+
+double short_march_us(int dtype, int K, int cols_per_lane, int H, long long waves,
+                      long long cells) {
+    const int simds = 4 * compute_units();
+    const double rows = (double)H * K + (double)K * K, mega = 1e-6 * (double)cells;
+    const double share = (double)((waves + simds - 1) / simds);
+    if (dtype == SSLBM_F64)
+        return 2.94 + rows * (0.047 + 0.074 * share) + 7.97 * mega;
+    return cols_per_lane == 2 ? 2.51 + rows * (0.137 + 0.007 * share) + 4.51 * mega
+                              : 2.45 + rows * (0.060 + 0.039 * share) + 3.72 * mega;
+}
+
 bool tiles_pay(int dtype, const GridSize *sizes, int n, double march_us) {
     constexpr int LONG = 1000;
     return tile_plan(dtype, sizes, n, LONG).us <= 1.05 * LONG * march_us;

@@ -8,14 +8,14 @@ from paper_2603_19789_amd import inputs
 pytestmark = pytest.mark.gpu
 
 # (dtype, rows a lane, steps, sizes): ragged last tiles in both directions
-HEIGHTS = [("f32", 2, 7, [(300, 201), (129, 255)] * 2),
-           ("f32", 3, 7, [(300, 201), (129, 255)] * 3),
-           ("f32", 4, 17, [(520, 510), (257, 129), (199, 200)]),
-           ("f32", 5, 17, [(512, 510), (384, 301)] * 3),
-           ("f32", 7, 7, [(512, 510), (384, 301)] * 3),
-           ("f64", 1, 7, [(101, 67), (70, 45)]),
-           ("f64", 2, 7, [(257, 255), (301, 199), (130, 120)]),
-           ("f64", 3, 7, [(520, 510), (257, 129), (199, 200)])]
+HEIGHTS = [("f32", 2, 33, [(257, 255), (301, 199), (130, 120)]),
+           ("f32", 3, 25, [(300, 201), (129, 255)] * 2),
+           ("f32", 4, 33, [(512, 510), (384, 301)] * 3),
+           ("f32", 5, 37, [(512, 510), (384, 301)] * 3),
+           ("f32", 7, 29, [(600, 500)] * 4),
+           ("f64", 1, 25, [(101, 67), (70, 45)]),
+           ("f64", 2, 29, [(257, 255), (301, 199), (130, 120)]),
+           ("f64", 3, 29, [(520, 510), (257, 129), (199, 200)])]
 
 
 @pytest.mark.parametrize("bc", ["periodic", "noflux"])

@@ -83,6 +83,47 @@ for (nx, ny), want in {ROUTES[dtype]!r}:
     assert not bad, bad
 
 
+# (nx, ny, steps) -> kernels: short runs by their own estimate, grids of few tiles
+# and thin ones as long runs
+SHORT = {
+    "f32": [((128, 128), 5, "tile"), ((768, 768), 2, "march"), ((768, 768), 14, "tile"),
+            ((1024, 1024), 4, "march"), ((1024, 1024), 16, "tile"), ((1024, 1024), 25, "tile"),
+            ((1500, 901), 7, "march"), ((3000, 200), 5, "march"), ((10000, 40), 5, "tile"),
+            ((400, 400), 12, "tile")],
+    "f64": [((128, 128), 12, "tile"), ((400, 400), 14, "tile"), ((670, 670), 12, "tile"),
+            ((4096, 64), 2, "march"), ((670, 670), 3, "march"), ((670, 670), 60, "tile")],
+}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_short_runs_take_the_faster_passes(dtype):
+    """A single grid's run and its plan, and an ensemble of one such grid, whose
+    passes all have the rows of its deepest one."""
+    result = record(f'''
+result = []
+for (nx, ny), steps, want in {SHORT[dtype]!r}:
+    h = context(nx, ny, {dtype!r})
+    single = [k for k in passes(lambda: lib.sslbm_run(h, rho, scratch, steps, None))
+              if k[0] != "copy"]
+    n, hi, lo = ctypes.c_longlong(), ctypes.c_int(), ctypes.c_int()
+    lib.sslbm_plan_run(h, steps, ctypes.byref(n), ctypes.byref(hi), ctypes.byref(lo))
+    e = ensemble([(nx, ny)], {dtype!r})
+    many = "tile"
+    if 5 * nx * ny * {4 if dtype == "f32" else 8} > 81920:
+        kinds = passes(lambda: lib.sslbm_ensemble_run(e, rho, scratch, steps, 0, None))
+        many = "tile" if kinds[0][0] == "tile" else "march"
+    result.append([nx, ny, steps, want, sorted({{k[0] for k in single}}), len(single) == n.value,
+                   many])
+''')
+    bad = [r for r in result if r[4] != [r[3]] or not r[5]]
+    assert not bad, bad
+    one = {tuple(r[:3]): r[6] for r in result}
+    if dtype == "f32":
+        assert one[1500, 901, 7] == "march" and one[1024, 1024, 16] == "tile"
+    else:
+        assert one[670, 670, 3] == "march" and one[670, 670, 12] == "tile"
+
+
 def test_marches_of_a_tuned_context_have_the_tuned_rows():
     """After a tuning that tiles won, marches (single steps, recorded runs
     every second step) run the shape that was timed, columns and rows."""
