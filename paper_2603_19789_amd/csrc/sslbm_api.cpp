@@ -133,14 +133,30 @@ sslbm_launch resolve(const sslbm_ctx *c) {
     return r;
 }
 
+// Steps per pass of a run of nsteps. FP64 with a diffusing D goes back from four
+// to five where that saves passes and at most half of them have the fifth step
+// (9 steps of 1024^2: (5, 4) 53 us, (3, 2, 2, 2) 69).
+int run_depth(const sslbm_ctx *c, long long nsteps) {
+    const int K = resolve(c).steps_per_pass;
+    if (c->dtype == SSLBM_F64 && K == 4 && requested(c).steps_per_pass == 0) {
+        const sslbm::PassPlan at4 = sslbm::plan_passes(nsteps, 4);
+        const sslbm::PassPlan at5 = sslbm::plan_passes(nsteps, 5);
+        if (at5.count < at4.count && at5.base == 4 && 2 * at5.longer <= at5.count)
+            return 5;
+    }
+    return K;
+}
+
 // Most steps of a march pass in a run of nsteps. A segment that one wavefront can
 // hold is one pass, whatever the context's steps per pass: a state less through
 // HBM each way than in two passes (FP32 4096^2 every 8 steps: 2247 us for 64
 // steps, 2741 in passes of four; FP64 with a diffusing D every 5: 2827 us for 40
 // steps although that kernel spills, 5449 in passes of three and two).
 int march_depth(const sslbm_ctx *c, long long nsteps, bool segment) {
-    return segment && nsteps <= sslbm::march_max_depth(c->dtype, 1) ? (int)nsteps
-                                                                    : resolve(c).steps_per_pass;
+    if (!segment)
+        return run_depth(c, nsteps);
+    return nsteps <= sslbm::march_max_depth(c->dtype, 1) ? (int)nsteps
+                                                         : resolve(c).steps_per_pass;
 }
 
 // Tiles of a run of nsteps (of a segment: with the fewest passes): none (rows =
@@ -558,7 +574,7 @@ sslbm_status sslbm_plan_run(const sslbm_ctx *c, long long nsteps, long long *pas
     if (!c || nsteps < 0 || !passes)
         return SSLBM_E_ARG;
     const sslbm::TilePlan tiles = run_tiles(c, nsteps);
-    report_plan(sslbm::plan_passes(nsteps, tiles.rows ? tiles.depth : resolve(c).steps_per_pass),
+    report_plan(sslbm::plan_passes(nsteps, tiles.rows ? tiles.depth : run_depth(c, nsteps)),
                 passes, longest, shortest);
     return SSLBM_OK;
 }
@@ -597,7 +613,7 @@ sslbm_status sslbm_run(sslbm_ctx *c, void *rho, void *scratch, long long nsteps,
     if (nsteps == 0)
         return SSLBM_OK;
     const sslbm::TilePlan tiles = run_tiles(c, nsteps);
-    const int K = tiles.rows ? tiles.depth : resolve(c).steps_per_pass;
+    const int K = tiles.rows ? tiles.depth : run_depth(c, nsteps);
     const hipStream_t s = (hipStream_t)hip_stream;
     const sslbm::GridDesc g = grid_of(c);
     void *src = rho, *dst = scratch;

@@ -195,6 +195,25 @@ for n, d in ((1500, 3e-3), (1700, 3e-3), (1800, 3e-3), (2048, 3e-3), (4096, 3e-3
     assert result == [[4, 6], [4, 6], [5, 6], [5, 6], [5, 6], [5, 6], [5, 6]]
 
 
+def test_five_steps_where_they_save_passes():
+    """FP64 with a diffusing D, four steps a pass: five where that saves passes
+    and at most half of them take the fifth step."""
+    result = record('''
+result = []
+for steps in (4, 5, 8, 9, 10, 12, 16, 17, 18, 19, 60):
+    h = context(1024, 1024, "f64", 3e-3)
+    ks = [k[1] for k in passes(lambda: lib.sslbm_run(h, rho, scratch, steps, None))]
+    n, hi, lo = ctypes.c_longlong(), ctypes.c_int(), ctypes.c_int()
+    lib.sslbm_plan_run(h, steps, ctypes.byref(n), ctypes.byref(hi), ctypes.byref(lo))
+    assert [n.value, hi.value, lo.value] == [len(ks), max(ks), min(ks)]
+    assert lib.sslbm_set_blocking(h, 4) == 0
+    assert max(k[1] for k in passes(lambda: lib.sslbm_run(h, rho, scratch, steps, None))) <= 4
+    result.append([steps, len(ks), max(ks)])
+''')
+    assert result == [[4, 2, 2], [5, 2, 3], [8, 2, 4], [9, 2, 5], [10, 4, 3], [12, 4, 3], [16, 4, 4],
+                      [17, 4, 5], [18, 4, 5], [19, 6, 4], [60, 16, 4]]
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 def test_finite_difference_tiles_fit_low_grids(dtype):
     """The finite-difference step takes low tiles on grids of a few rows,
