@@ -134,17 +134,24 @@ sslbm_launch resolve(const sslbm_ctx *c) {
 }
 
 // Steps per pass of a run of nsteps. FP64 with a diffusing D goes back from four
-// to five where that saves passes and at most half of them have the fifth step
-// (9 steps of 1024^2: (5, 4) 53 us, (3, 2, 2, 2) 69).
+// to five where the passes, whose number is even, are estimated to take less
+// time so (1300^2: 9 steps as (5, 4) 70 us, as (3, 2, 2, 2) 99; 10 steps 84 and 99;
+// 20 steps 166 and 157). The estimate: a pass of up to four steps by its cells and
+// steps, the five-step kernel, which spills, by its cells, within 7% of passes
+// measured from 1024^2 to 1600^2.
 int run_depth(const sslbm_ctx *c, long long nsteps) {
     const int K = resolve(c).steps_per_pass;
-    if (c->dtype == SSLBM_F64 && K == 4 && requested(c).steps_per_pass == 0) {
-        const sslbm::PassPlan at4 = sslbm::plan_passes(nsteps, 4);
-        const sslbm::PassPlan at5 = sslbm::plan_passes(nsteps, 5);
-        if (at5.count < at4.count && at5.base == 4 && 2 * at5.longer <= at5.count)
-            return 5;
-    }
-    return K;
+    if (c->dtype != SSLBM_F64 || K != 4 || requested(c).steps_per_pass != 0)
+        return K;
+    const double mega = 1e-6 * (double)plane_elems(c);
+    auto pass = [&](int k) {
+        return k == 5 ? 17.8 + 13.4 * mega : 2.2 + 9.3 * mega + (2.0 + 0.3 * mega) * k;
+    };
+    auto run = [&](int depth) {
+        const sslbm::PassPlan p = sslbm::plan_passes(nsteps, depth);
+        return (double)p.longer * pass(p.base + 1) + (double)(p.count - p.longer) * pass(p.base);
+    };
+    return run(5) < run(4) ? 5 : 4;
 }
 
 // Most steps of a march pass in a run of nsteps. A segment that one wavefront can

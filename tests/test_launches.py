@@ -196,8 +196,8 @@ for n, d in ((1500, 3e-3), (1700, 3e-3), (1800, 3e-3), (2048, 3e-3), (4096, 3e-3
 
 
 def test_five_steps_where_they_save_passes():
-    """FP64 with a diffusing D, four steps a pass: five where that saves passes
-    and at most half of them take the fifth step."""
+    """FP64 with a diffusing D, four steps a pass on grids that the last-level
+    cache holds: five where a run's passes take less time so."""
     result = record('''
 result = []
 for steps in (4, 5, 8, 9, 10, 12, 16, 17, 18, 19, 60):
@@ -210,7 +210,7 @@ for steps in (4, 5, 8, 9, 10, 12, 16, 17, 18, 19, 60):
     assert max(k[1] for k in passes(lambda: lib.sslbm_run(h, rho, scratch, steps, None))) <= 4
     result.append([steps, len(ks), max(ks)])
 ''')
-    assert result == [[4, 2, 2], [5, 2, 3], [8, 2, 4], [9, 2, 5], [10, 4, 3], [12, 4, 3], [16, 4, 4],
+    assert result == [[4, 2, 2], [5, 2, 3], [8, 2, 4], [9, 2, 5], [10, 2, 5], [12, 4, 3], [16, 4, 4],
                       [17, 4, 5], [18, 4, 5], [19, 6, 4], [60, 16, 4]]
 
 
