@@ -179,8 +179,16 @@ sslbm_status sslbm_model_run(sslbm_model *m, void *rho, void *scratch, long long
     const int K = resolved_blocking(m);
     void *src = rho, *dst = scratch;
     // an even number of passes where every one keeps a step, so that the
-    // result ends in rho
-    const sslbm::PassPlan plan = sslbm::plan_passes(nsteps, K);
+    // result ends in rho; but a run that one pass can take does so, with a copy
+    // after it, where that is faster than two passes: two steps where two states
+    // do not fit the 256 MB last-level cache (D2Q5, one pass and two: FP32 4096^2
+    // 399 and 494 us, 2600^2 150 and 162, FP64 2048^2 197 and 212; 1600^2 102 and
+    // 94), three where they are three times as large (FP32 4096^2 412 and 490,
+    // FP64 2048^2 229 and 212)
+    const size_t cache = (size_t)256 << 20;
+    const bool one = nsteps <= K && 2 * bytes >= (nsteps <= 2 ? cache : 3 * cache);
+    const sslbm::PassPlan plan =
+        one ? sslbm::fewest_passes(nsteps, K) : sslbm::plan_passes(nsteps, K);
     for (long long i = 0; i < plan.count; ++i) {
         const int k = plan.steps(i);
         const sslbm_status st = hip_status(m, sslbm::launch_model(m->dtype, m->lattice, src, dst,

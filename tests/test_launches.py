@@ -326,6 +326,26 @@ for groups, want in {MIXED!r}:
     assert result[0][3] == [1, 2] and result[3][3] == [2, 1]  # by class, in order of size
 
 
+def test_model_runs_of_one_pass():
+    """A generic model's run that one pass can take: one pass and a copy on
+    large grids, two passes where the last-level cache holds the states."""
+    result = record('''
+from paper_2603_19789_amd import Model
+result = []
+for dtype, n, steps in (("f32", 1024, 2), ("f32", 2600, 2), ("f32", 2600, 3), ("f32", 4096, 3),
+                        ("f64", 1600, 2), ("f64", 2048, 2), ("f64", 2048, 3), ("f64", 4096, 3),
+                        ("f32", 4096, 1), ("f32", 4096, 4), ("f32", 4096, 6), ("f32", 4096, 7)):
+    m = Model(n, n, inputs.seirvd_model(lattice=5), dtype=dtype)
+    kinds = [k[0] for k in passes(lambda: lib.sslbm_model_run(m.handle, rho, scratch, steps, None))]
+    result.append([dtype, n, steps, len(kinds) - kinds.count("copy"), kinds.count("copy")])
+''')
+    want = {("f32", 1024, 2): (2, 0), ("f32", 2600, 2): (1, 1), ("f32", 2600, 3): (2, 0),
+            ("f32", 4096, 3): (1, 1), ("f64", 1600, 2): (2, 0), ("f64", 2048, 2): (1, 1),
+            ("f64", 2048, 3): (2, 0), ("f64", 4096, 3): (1, 1), ("f32", 4096, 1): (1, 1),
+            ("f32", 4096, 4): (2, 0), ("f32", 4096, 6): (2, 0), ("f32", 4096, 7): (4, 0)}
+    assert {tuple(r[:3]): tuple(r[3:]) for r in result} == want
+
+
 def test_an_ensemble_run_is_planned_once():
     """A run that repeats the last one's steps makes no new plan; one with other
     steps, or after a change of shapes, does."""
