@@ -107,13 +107,15 @@ double march_us(int dtype, int K, int cols_per_lane, int H, long long waves);
 // march_us a step (asked where tiles are not few: runs of every length then take
 // the same kind of pass).
 bool tiles_pay(int dtype, const GridSize *sizes, int n, double march_us);
-// Runs of up to so many steps are estimated by themselves, on grids of at least
-// SHORT_RUN_SIDE cells each way: the time in us of the tile passes `plan` over n
-// grid sizes, and of one march pass over grids of so many cells.
+// Runs of up to so many steps are estimated by themselves: the time in us of the
+// tile passes `plan` over n grid sizes, and of one march pass over grids of so
+// many cells. Grids of fewer than SHORT_RUN_SIDE cells one way (`thin`) have an
+// estimate in FP64 only.
 constexpr int SHORT_RUN = 24, SHORT_RUN_SIDE = 64;
-double short_tiles_us(int dtype, const GridSize *sizes, int n, int R, const PassPlan &plan);
+double short_tiles_us(int dtype, const GridSize *sizes, int n, int R, const PassPlan &plan,
+                      bool thin = false);
 double short_march_us(int dtype, int K, int cols_per_lane, int H, long long waves,
-                      long long cells);
+                      long long cells, bool thin = false);
 // Compute units of the current device (256 where it cannot be asked).
 int compute_units();
 // K steps in -> out (no overlap) with R rows a lane.

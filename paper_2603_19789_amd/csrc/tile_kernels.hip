@@ -114,7 +114,12 @@ TilePlan tile_plan(int dtype, const GridSize *sizes, int n, long long nsteps, bo
 // 0.4% of the faster kind on the mean and 12% at most; with tiles wherever a
 // long run takes them it was 7% and 45% (5 steps, FP32: 1500 x 901 30.1 us of
 // tiles, 23.2 of marches; 1024^2 23.9 and 20.8; 768^2 16.2 and 14.7).
-double short_tiles_us(int dtype, const GridSize *sizes, int n, int R, const PassPlan &plan) {
+// Thin grids in FP64: 20 of them, 9% rms, with the cells that tiles and marches
+// load; 1.3% on the mean and 26% at most, 7% and 67% by the long run (3 steps of
+// 20000 x 13: 29.3 us of tiles, 18.7 of marches). In FP32 such a fit would send as
+// many thin grids to the slower kind as it takes from it.
+double short_tiles_us(int dtype, const GridSize *sizes, int n, int R, const PassPlan &plan,
+                      bool thin) {
     const int cus = compute_units();
     long long cells = 0;
     for (int i = 0; i < n; ++i)
@@ -128,6 +133,9 @@ double short_tiles_us(int dtype, const GridSize *sizes, int n, int R, const Pass
         for (int s = 1; s <= k; ++s)
             rows += (TILE_WAVES - 2 * (s / R)) * R / 4;
         const double rounds = (double)((tiles + cus - 1) / cus);
+        if (thin)
+            return 0.22 + 0.46 * k + rounds * (1.64 + 0.133 * rows) +
+                   1.36e-6 * (double)(tiles * 64 * TILE_WAVES * R) + 7.13 * mega;
         return dtype == SSLBM_F32 ? 2.46 + 0.289 * k + 0.075 * rounds * rows + 4.76 * mega
                                   : 0.295 * k + rounds * (3.0 + 0.139 * rows) + 8.31 * mega;
     };
@@ -137,10 +145,13 @@ double short_tiles_us(int dtype, const GridSize *sizes, int n, int R, const Pass
 }
 
 double short_march_us(int dtype, int K, int cols_per_lane, int H, long long waves,
-                      long long cells) {
+                      long long cells, bool thin) {
     const int simds = 4 * compute_units();
     const double rows = (double)H * K + (double)K * K, mega = 1e-6 * (double)cells;
     const double share = (double)((waves + simds - 1) / simds);
+    if (thin)
+        return 3.35 + rows * (0.053 + 0.074 * share + (share > 2.0 ? 0.072 * (share - 2.0) : 0.0)) +
+               (double)waves * (0.72e-4 + 0.51e-6 * 64 * (H + 2 * K)) + 7.96 * mega;
     if (dtype == SSLBM_F64)
         return 2.94 + rows * (0.047 + 0.074 * share) + 7.97 * mega;
     return cols_per_lane == 2 ? 2.51 + rows * (0.137 + 0.007 * share) + 4.51 * mega

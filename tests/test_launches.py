@@ -84,14 +84,16 @@ for (nx, ny), want in {ROUTES[dtype]!r}:
 
 
 # (nx, ny, steps) -> kernels: short runs by their own estimate, grids of few tiles
-# and thin ones as long runs
+# and in FP32 thin ones as long runs
 SHORT = {
     "f32": [((128, 128), 5, "tile"), ((768, 768), 2, "march"), ((768, 768), 14, "tile"),
             ((1024, 1024), 4, "march"), ((1024, 1024), 16, "tile"), ((1024, 1024), 25, "tile"),
             ((1500, 901), 7, "march"), ((3000, 200), 5, "march"), ((10000, 40), 5, "tile"),
             ((400, 400), 12, "tile")],
     "f64": [((128, 128), 12, "tile"), ((400, 400), 14, "tile"), ((670, 670), 12, "tile"),
-            ((4096, 64), 2, "march"), ((670, 670), 3, "march"), ((670, 670), 60, "tile")],
+            ((4096, 64), 2, "march"), ((670, 670), 3, "march"), ((670, 670), 60, "tile"),
+            ((20000, 13), 3, "march"), ((5000, 60), 3, "march"), ((8, 12000), 4, "march"),
+            ((8000, 30), 12, "tile"), ((5000, 60), 14, "tile")],
 }
 
 
