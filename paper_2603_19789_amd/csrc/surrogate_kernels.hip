@@ -433,13 +433,13 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
     const bool cload = tid < TC / 4;
 
     // weight pieces: row (tap t, position 16 ns + 4 q + i) of Bs, which holds
-    // output channel 4 NT q + 4 ns + i of the group, 8 channels hk of the
-    // chunk; channels past the layer's load its last one (their results are
+    // output channel 4 NT q + 4 ns + i of the group (FP32 output: 16 ns + 4 q +
+    // i, see the epilogue), 8 channels hk of the chunk; channels past the layer's load its last one (their results are
     // never stored). Piece j of a thread is row (tid >> 2) + 64 j: the same
     // position for every j, 64 / TC taps apart.
     const int hk = 8 * (tid & 3);
     const int bpos = (tid >> 2) % TC, btap = (tid >> 2) / TC;
-    const int bo = 4 * NT * (bpos / 4 % 4) + 4 * (bpos / 16) + bpos % 4;
+    const int bo = F32OUT ? bpos : 4 * NT * (bpos / 4 % 4) + 4 * (bpos / 16) + bpos % 4;
     const int blds = (tid >> 2) * 32 + (hk ^ 8 * lds_turn(bpos));
     auto bst = [&](int j) { return btap + 64 / TC * j < 9; };
     const unsigned bstep = (unsigned)(64 / TC * a.cin * 2);
@@ -638,12 +638,18 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
     // MB, 4.2 TB/s), pooled 41 -> 35, through a mask 58 -> 42; 64 channels of
     // 128^2 pixels 27 -> 25, pooled 34 -> 29, through a mask 44 -> 32; the
     // decoders' backward data 83 -> 71.
+    // FP32 outputs keep tile ns at channels 16 ns + 4 g: four lanes then cover 64
+    // bytes of a pixel with one access, where 4 NT consecutive channels a lane
+    // would leave 16 bytes of every 64 (16 images' worth of 256^2 pixels in four,
+    // 64 -> 64 channels: 39 us so, 29 with whole pieces).
     constexpr int PAIRS = 2 * NT;  // channel pairs of a lane
+    constexpr int LANE_C = F32OUT ? 4 : 4 * NT;   // from lane group to lane group
+    constexpr int TILE_C = F32OUT ? 16 : 4;       // from tile to tile of a lane
     auto epilogue = [&](int unit, const float *bias) {
         int n, y0, x0, cg;
         unit_origin(unit, n, y0, x0, cg);
         const int yr = y0 + 2 * wv;  // the wavefront's first row (even)
-        const int c0 = cg * TC + 4 * NT * g;
+        const int c0 = cg * TC + LANE_C * g;
         // UPB: the lane's channels belong to the upsampled input (cd is a
         // multiple of 16, so all of them or none)
         const bool up_block = UPB && c0 < a.cd;
@@ -678,7 +684,7 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
                 const unsigned off = x_ok[half] ? yrow + yoff[half] : OUT_OF_RANGE;
 #pragma unroll
                 for (int ns = 0; ns < NT; ++ns) {
-                    const f32x4 b = *reinterpret_cast<const f32x4 *>(&bias[4 * NT * g + 4 * ns]);
+                    const f32x4 b = *reinterpret_cast<const f32x4 *>(&bias[LANE_C * g + TILE_C * ns]);
                     f32x4 v;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -689,7 +695,9 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
                     if constexpr (F32OUT) {
                         __builtin_amdgcn_raw_buffer_store_b128(
                             __builtin_bit_cast(u32x4, v), yr_,
-                            c0 + 4 * ns < a.cout ? off + (unsigned)(16 * ns) : OUT_OF_RANGE, 0, 0);
+                            c0 + TILE_C * ns < a.cout ? off + (unsigned)(4 * TILE_C * ns)
+                                                      : OUT_OF_RANGE,
+                            0, 0);
                     } else {
                         hv[ms][2 * ns] = pack_bf16x2(v[0], v[1]);
                         hv[ms][2 * ns + 1] = pack_bf16x2(v[2], v[3]);
