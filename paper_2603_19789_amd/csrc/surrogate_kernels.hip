@@ -640,8 +640,8 @@ void conv_halo_kernel(ConvArgs a, int tiles_x, int tiles_y, int units) {
     // decoders' backward data 83 -> 71.
     // FP32 outputs keep tile ns at channels 16 ns + 4 g: four lanes then cover 64
     // bytes of a pixel with one access, where 4 NT consecutive channels a lane
-    // would leave 16 bytes of every 64 (16 images' worth of 256^2 pixels in four,
-    // 64 -> 64 channels: 39 us so, 29 with whole pieces).
+    // would leave gaps of 48 (four images of 256^2 pixels, 64 -> 64 channels:
+    // 39 us with the gaps, 30 without).
     constexpr int PAIRS = 2 * NT;  // channel pairs of a lane
     constexpr int LANE_C = F32OUT ? 4 : 4 * NT;   // from lane group to lane group
     constexpr int TILE_C = F32OUT ? 16 : 4;       // from tile to tile of a lane
