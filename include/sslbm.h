@@ -155,8 +155,8 @@ int sslbm_get_blocking(const sslbm_ctx *c);
  * With every field automatic, sslbm_run takes grids of at most 1.4 million
  * cells in FP32 (0.45 million in FP64) in passes of tiles held in registers
  * instead, of up to 16 steps, unless it estimates the march to be faster (as on
- * long grids of a few rows or columns); the shape reported is then the one that passes
- * of the march would have. sslbm_plan_run reports the passes either way.
+ * long grids of a few rows or columns, or for a few steps); the shape reported is
+ * then the one that passes of the march would have. sslbm_plan_run reports the passes either way.
  */
 typedef struct {
     int steps_per_pass;
@@ -226,7 +226,8 @@ sslbm_status sslbm_run(sslbm_ctx *c, void *rho, void *scratch, long long nsteps,
 /*
  * How sslbm_run splits nsteps into passes with the context's current pass
  * shape: the fewest passes of at most steps_per_pass steps (of the depth chosen
- * for nsteps where it takes tiles), one more if that
+ * for nsteps where it takes tiles, or four or five steps in FP64 with a
+ * diffusing D and an automatic depth of four), one more if that
  * makes their count even and leaves every pass a step (the ping-pong then
  * ends in rho, with no copy), and the steps spread evenly over them: the
  * first passes take *longest steps, the rest *shortest (equal when the split
